@@ -636,8 +636,9 @@ def kernel_name(c, bf16: bool, planned: bool = False, persistent: bool = False,
                 plan_arith: int = 1, paired: bool = False) -> str:
     """The kernel libbsr's automatic choice launches for this product: the flat-stream kernel
     for 32x1 and 16x1 (its planned form with a plan), the matrix-core tiled kernel for square
-    blocks, else the vector-ALU tile kernel, each in its column-chunked form when the 32-token
-    X tile does not fit in LDS, else the generic kernel.  (A label: the library's plan decides,
+    blocks, the small-block matrix-core kernel for blocks of 4 or 8 rows and enough work, else
+    the vector-ALU tile kernel, each in its column-chunked form when the X tile does not fit in
+    LDS, else the generic kernel.  (A label: the library's plan decides,
     and the kernel trace shows what ran.)"""
     shape = (c["R"], c["C"])
     flag = "true" if bf16 else "false"
@@ -658,6 +659,10 @@ def kernel_name(c, bf16: bool, planned: bool = False, persistent: bool = False,
         if fits:
             return f"spmm_tiled_kernel<{c['R']}, {c['C']}, 16, {flag}, {w}>"
         return f"spmm_kchunk_kernel<{c['R']}, {c['C']}, {flag}, {w}>"
+    macs = c["k"] * c["R"] * c["C"] * c["T"]
+    if shape in ((8, 8), (4, 4), (8, 1), (4, 1)):
+        if macs >= ((16 if bf16 else 128 if fits else 192) << 20):
+            return f"spmm_mtile_kernel<{c['R']}, {c['C']}, {flag}, {'false' if fits else 'true'}>"
     if shape in VALU_SHAPES and not (bf16 and shape == (1, 1)):
         kern = "spmm_vtile_kernel" if fits else "spmm_vtile_chunk_kernel"
         return f"{kern}<{c['R']}, {c['C']}, {flag}>"

@@ -246,7 +246,7 @@ bsr_status bsr_spmm_batched_planned(const bsr_spmm_item_t *items, const bsr_plan
     // or, when its X tile is too wide for LDS, to the column-chunked matrix-core kernel; else to
     // the vector-ALU tile kernel or its column-chunked form; else to the generic kernel (a
     // forced kernel choice narrows this; a forced kernel that does not fit is an error).
-    enum Kind { kGeneric = 0, kTiled = 1, kVtile = 2, kKchunk = 3, kVchunk = 4, kFlat = 5 };
+    enum Kind { kGeneric = 0, kTiled = 1, kVtile = 2, kKchunk = 3, kVchunk = 4, kFlat = 5, kMtile = 6 };
     std::vector<int> work;
     for (int32_t i = 0; i < n_items; ++i)
         if (items[i].T > 0) work.push_back(i);
@@ -257,6 +257,7 @@ bsr_status bsr_spmm_batched_planned(const bsr_spmm_item_t *items, const bsr_plan
     const size_t lds_limit = bsr::device_lds_per_block();
     std::vector<bsr::TiledWork> tiled(work.size());
     std::vector<bsr::KchunkWork> kchunk(work.size());
+    std::vector<bsr::MtileWork> mtile(work.size());
     std::vector<int> kind(work.size(), kGeneric);
     std::vector<int> tokens(work.size(), 32);   // tokens per tile of a flat or tiled launch
     for (size_t w = 0; w < work.size(); ++w) {
@@ -271,7 +272,14 @@ bsr_status bsr_spmm_batched_planned(const bsr_spmm_item_t *items, const bsr_plan
                  bsr::tiled_supported(R, C, dt) &&
                  bsr::plan_kchunk(it.X, it.T, it.ldx, it.W, it.ldy, 1, lds_limit).base.ok)
             kind[w] = kKchunk;
-        else if ((kernel == BSR_KERNEL_AUTO || kernel == BSR_KERNEL_VALU) &&
+        else if (const bsr::MtilePlan mp =
+                     kernel == BSR_KERNEL_AUTO
+                         ? bsr::plan_mtile(it.X, it.T, it.ldx, it.W, it.ldy, 1, lds_limit)
+                         : bsr::MtilePlan{};
+                 mp.ok) {
+            kind[w] = kMtile;
+            tokens[w] = mp.tokens;
+        } else if ((kernel == BSR_KERNEL_AUTO || kernel == BSR_KERNEL_VALU) &&
                  bsr::vtile_supported(R, C, dt) &&
                  bsr::plan_vtile(it.X, it.T, it.ldx, it.W, it.ldy, 1, lds_limit).ok)
             kind[w] = kVtile;
@@ -326,18 +334,54 @@ bsr_status bsr_spmm_batched_planned(const bsr_spmm_item_t *items, const bsr_plan
     for (size_t w = 0; w < work.size(); ++w)
         if (kind[w] == kGeneric) launches.push_back(Launch{kGeneric, {int(w)}});
 
+    auto launch_slices = [&](const Launch &l) {
+        std::vector<int64_t> tiles;
+        for (int w : l.members)
+            tiles.push_back((items[work[w]].T + tokens[w] - 1) / tokens[w]);
+        return bsr::auto_slices(tiles.data(), int(tiles.size()), cus);
+    };
+    // Small-block products whose input is staged in column chunks may need more slices than the
+    // launch's automatic count (their running sums share LDS with the tile).  When that would
+    // start a second round of workgroups, they get a launch of their own, in which each kind has
+    // the whole chip: BERT-base's feed-forward pair in 8x8 blocks at 4096 tokens takes 88 us in
+    // two launches and 102 us in one; at 777 tokens (4x4, bf16), where one round holds both, 35
+    // and 25 us (MI355X).
+    if (slices == 0) {
+        for (size_t li = 0; li < launches.size(); ++li) {
+            if (launches[li].kind != kMtile) continue;
+            const int S = launch_slices(launches[li]);
+            int64_t wgs = 0;
+            std::vector<int> whole, chunked;
+            for (int w : launches[li].members) {
+                const bsr_spmm_item_t &it = items[work[w]];
+                const bsr::MtilePlan p =
+                    bsr::plan_mtile(it.X, it.T, it.ldx, it.W, it.ldy, S, lds_limit);
+                wgs += (int64_t(p.num_tiles) * p.slices + 7) / 8 * 8;
+                (p.nchunks > 1 ? chunked : whole).push_back(w);
+            }
+            if (wgs > cus && !whole.empty() && !chunked.empty()) {
+                launches[li].members = whole;
+                launches.insert(launches.begin() + li + 1, Launch{kMtile, chunked});
+                ++li;
+            }
+        }
+    }
+
     // Slices per launch: the automatic count is chosen for the token tiles of the products
     // that share the launch (launches run one after another).
     for (const Launch &l : launches) {
         if (l.kind == kGeneric) continue;
-        std::vector<int64_t> tiles;
-        for (int w : l.members)
-            tiles.push_back((items[work[w]].T + tokens[w] - 1) / tokens[w]);
-        const int auto_S = bsr::auto_slices(tiles.data(), int(tiles.size()), cus);
+        const int auto_S = launch_slices(l);
         for (int w : l.members) {
             const bsr_spmm_item_t &it = items[work[w]];
             const int64_t Nb = it.W->n_rows / it.W->R;
             const int S = slices > 0 ? slices : int(auto_S < Nb ? auto_S : Nb);
+            if (kind[w] == kMtile) {
+                mtile[w] = bsr::MtileWork{
+                    bsr::plan_mtile(it.X, it.T, it.ldx, it.W, it.ldy, S, lds_limit), it.X, it.T,
+                    it.ldx, it.W, it.bias, it.Y, it.ldy};
+                continue;
+            }
             if (kind[w] == kKchunk || kind[w] == kVchunk) {
                 const bsr::KchunkPlan kp =
                     kind[w] == kKchunk
@@ -373,6 +417,10 @@ bsr_status bsr_spmm_batched_planned(const bsr_spmm_item_t *items, const bsr_plan
             s = l.kind == kKchunk
                     ? bsr::launch_spmm_kchunk(batch, int(l.members.size()), stream, lev)
                     : bsr::launch_spmm_vchunk(batch, int(l.members.size()), stream, lev);
+        } else if (l.kind == kMtile) {
+            bsr::MtileWork batch[bsr::kMaxItems];
+            for (size_t m = 0; m < l.members.size(); ++m) batch[m] = mtile[l.members[m]];
+            s = bsr::launch_spmm_mtile(batch, int(l.members.size()), stream, lev);
         } else if (l.kind != kGeneric) {
             bsr::TiledWork batch[bsr::kMaxItems];
             for (size_t m = 0; m < l.members.size(); ++m) batch[m] = tiled[l.members[m]];

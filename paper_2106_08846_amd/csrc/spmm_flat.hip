@@ -47,40 +47,6 @@ constexpr int kRingOf = kDepthOf<PK> + 1;
 template <int PK>
 constexpr int kXChunksPersistent = PK == 2 ? 8 : 16;
 
-// A slice's units are shared out over the 16 waves by weights that depend on a wave's place
-// among the four waves of its SIMD (wave w runs on SIMD w % 4, after waves w - 4, w - 8, ...).
-// The SIMDs' instruction arbitration favours older waves: with equal shares the first wave of
-// every SIMD finished its stream about 30% before the last (per-wave timestamps on MI355X, the
-// BERT-large 32x1 stack), and the item waits for the last.  Weights 48:38:31:27 made that
-// launch 2% faster than equal shares (same box, A/B).  Start of wave l's units (l = 16: the end
-// of the range).
-constexpr unsigned kShareWeight[4] = {48, 38, 31, 27};
-constexpr unsigned kShareTotal = 4 * (kShareWeight[0] + kShareWeight[1] + kShareWeight[2] +
-                                      kShareWeight[3]);
-__device__ __forceinline__ int wave_start(int64_t Q0, unsigned span, unsigned l) {
-    const unsigned a = l >> 2, b = l & 3;
-    unsigned cum = 0;
-#pragma unroll
-    for (unsigned i = 0; i < 4; ++i) cum += i < a ? 4 * kShareWeight[i] : 0u;
-#pragma unroll
-    for (unsigned i = 0; i < 4; ++i) cum += i == a ? b * kShareWeight[i] : 0u;
-    return int(Q0) + int(uint64_t(span) * cum / kShareTotal);
-}
-
-// Inclusive prefix sum over the 64 lanes of a wave: row shifts by 1, 2, 4 and 8 lanes sum each
-// row of 16 lanes, then the last lane of row 0 is added to row 1 and of row 2 to row 3, and
-// the last lane of row 1 (now rows 0 and 1) to rows 2 and 3.  Lanes a shift reads from
-// outside their row contribute 0.
-__device__ __forceinline__ int wave_scan_incl(int v) {
-    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);   // row_shr:1
-    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);   // row_shr:2
-    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);   // row_shr:4
-    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);   // row_shr:8
-    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);   // row_bcast:15
-    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);   // row_bcast:31
-    return v;
-}
-
 // Empty owned rows, the stream and the combine of one (token tile, slice) item, shared by the
 // one-item and the persistent kernel.  `it` holds the wave's share and the LDS layout; the
 // ring holds the operands of the share's first kDepth units; fetch(ops, nvalid, u) loads

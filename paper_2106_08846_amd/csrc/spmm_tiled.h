@@ -173,6 +173,32 @@ struct KchunkWork {
 bsr_status launch_spmm_kchunk(const KchunkWork *work, int n, void *stream,
                               const LaunchEvents &ev);
 
+// The matrix-core kernel for blocks of 4 or 8 rows (4x1, 8x1, 4x4, 8x8): whole-row tiles, or
+// column chunks when the tile does not fit.
+struct MtilePlan {
+    bool ok = false;
+    int tokens = 32;        // tokens per tile
+    int num_tiles = 0, slices = 1;
+    int x_pitch = 0;        // LDS words between token rows
+    int chunk_blocks = 0;   // block-columns per chunk
+    int nchunks = 0;
+    int acc_words = 0, bias_words = 0, bound_words = 0, up_words = 0,   // LDS layout
+        stage_words = 0;   // Y staging buffers, 0 when they do not fit
+    size_t lds_bytes = 0;
+};
+struct MtileWork {
+    MtilePlan plan;
+    const void *X;
+    int64_t T, ldx;
+    const bsr_matrix_t *W;
+    const float *bias;
+    float *Y;
+    int64_t ldy;
+};
+MtilePlan plan_mtile(const void *X, int64_t T, int64_t ldx, const bsr_matrix_t *W, int64_t ldy,
+                     int slices, size_t lds_limit);
+bsr_status launch_spmm_mtile(const MtileWork *work, int n, void *stream, const LaunchEvents &ev);
+
 // The vector-ALU tile kernel (shapes without a matrix-core kernel: 1 x C, 2x1 .. 8x1, 2x2 ..
 // 8x8).  Same plan and batch structures; the plan fills num_tiles, slices, x_pitch, lds_bytes.
 bool vtile_supported(int R, int C, int dtype);

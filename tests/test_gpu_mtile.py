@@ -1,0 +1,107 @@
+"""The matrix-core kernel for blocks of 4 or 8 rows (4x1, 8x1, 4x4, 8x8) against the oracle.
+
+Sizes sit where it changes course (every product above the work at which the library takes it):
+token tiles of 32 and 64 with tails, one block-row, rows without blocks and full rows next to
+each other (units cut by wave boundaries), many rows per wave, inputs wide enough for several
+column chunks, layers too wide for staged stores, and forced slice counts.  Integer-valued inputs are exact in any order and must equal the generic
+kernel bit for bit; an infinite X element in a column no block reads must not show.
+"""
+import numpy as np
+import pytest
+import torch
+
+from paper_2106_08846_amd import bsr as B
+
+from .gpu_common import check_spmm, dev, host, log
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [(8, 8), (4, 4), (8, 1), (4, 1)]
+
+
+def matrix(N, K, R, C, density, seed, skew, integer=False):
+    """Dense W with a chosen block pattern (skew: empty, sparse and full rows in turn) as BSR."""
+    g = np.random.Generator(np.random.PCG64(seed))
+    Nb, Kb = N // R, K // C
+    mask = g.random((Nb, Kb)) < density
+    if skew:
+        mask[0::4] = False
+        mask[1::4] = True
+    W = g.integers(1, 5, (N, K)) if integer else g.standard_normal((N, K)) * 0.02 + 1e-3
+    W = (W * np.kron(mask, np.ones((R, C)))).astype(np.float32)
+    return B.bsr_prune_from_dense(dev(W), R, C, k=int(mask.sum()))
+
+
+def inputs(T, K, seed, bf16, integer=False):
+    g = np.random.Generator(np.random.PCG64(seed + 1))
+    X = (g.integers(-4, 5, (T, K)) if integer else g.standard_normal((T, K))).astype(np.float32)
+    Xd = dev(X)
+    return X, B.bsr_cast_f32_bf16(Xd) if bf16 else Xd
+
+
+CASES = [
+    # T, N, K (in blocks of 8), density, skew, slices
+    (22001, 8, 768, 1.0, False, None),  # one 8x8 block-row, the last tile nearly empty
+    (321, 1032, 768, 0.7, False, None), # a last tile of one token
+    (200, 2064, 768, 0.5, True, 1),     # one slice: rows cut between waves
+    (640, 3072, 136, 0.7, True, 1),     # many rows per wave
+    (97, 1032, 3072, 0.8, True, None),  # several column chunks, few rows per slice
+    (450, 768, 1544, 0.5, True, 2),     # chunks, rows cut by waves in every chunk
+    (95, 2312, 768, 0.9, False, 72),    # four block-rows of 8 per slice
+    (300, 1024, 1024, 0.5, True, 3),    # a tile that leaves no room for staged stores
+]
+
+
+@pytest.mark.parametrize("bf16", [False, True], ids=["f32", "bf16"])
+@pytest.mark.parametrize("R,C", SHAPES, ids=[f"{r}x{c}" for r, c in SHAPES])
+@pytest.mark.parametrize("case", range(len(CASES)))
+def test_mtile_against_oracle(device, case, R, C, bf16):
+    T, N, K, d, skew, slices = CASES[case]
+    log(f"mtile {R}x{C} {'bf16' if bf16 else 'f32'} T={T} {N}x{K} d={d} skew={skew} S={slices}")
+    M = matrix(N, K, R, C, d, case, skew)
+    bias = np.linspace(-1, 1, N).astype(np.float32)
+    X, Xd = inputs(T, K, case, bf16)
+    if bf16:
+        M = M.to_bf16()
+    Y = B.bsr_spmm_ex(Xd, M, dev(bias), None, kernel=None if slices is None else 0, slices=slices)
+    check_spmm(X, M, bias, Y, bf16=bf16)
+    again = B.bsr_spmm_ex(Xd, M, dev(bias), None, kernel=None if slices is None else 0,
+                          slices=slices)
+    assert torch.equal(Y, again), "not reproducible"
+    M = matrix(N, K, R, C, d, case, skew, integer=True)
+    X, Xd = inputs(T, K, case, bf16, integer=True)
+    if bf16:
+        M = M.to_bf16()
+    Yi = B.bsr_spmm_ex(Xd, M, None, None, kernel=None if slices is None else 0, slices=slices)
+    assert torch.equal(Yi, B.bsr_spmm_ex(Xd, M, None, None, kernel=B.KERNEL_GENERIC))
+
+
+@pytest.mark.parametrize("bf16", [False, True], ids=["f32", "bf16"])
+@pytest.mark.parametrize("R,C", SHAPES, ids=[f"{r}x{c}" for r, c in SHAPES])
+def test_mtile_infinities_and_pitch(device, R, C, bf16):
+    """Infinite X elements in columns without blocks never meet a padding weight; X and Y are
+    windows of wider tensors, at an odd column offset (fp32) or an even one (bf16)."""
+    T, N, K = 230, 1032, 768
+    M = matrix(N, K, R, C, 0.9, 7, False)
+    X, _ = inputs(T, K, 7, False)
+    # Free one block-column of blocks: rebuild without it.
+    dense = host(B.bsr_to_dense(M))
+    dense[:, :C] = 0.0
+    nz = int((np.abs(dense.reshape(N // R, R, K // C, C)).max((1, 3)) > 0).sum())
+    M = B.bsr_prune_from_dense(dev(dense), R, C, k=nz)
+    assert not (host(M.indices)[:nz] == 0).any()
+    if bf16:
+        M = M.to_bf16()
+    Xw = X.copy()
+    Xw[:, :C] = np.inf
+    off = 2 if bf16 else 1
+    big = torch.zeros((T, K + 10), device="cuda:0")
+    big[:, off:off + K] = dev(Xw)
+    if bf16:
+        big = B.bsr_cast_f32_bf16(big)
+    Yb = torch.full((T, N + 5), 7.0, device="cuda:0")
+    log(f"mtile inf/pitch {R}x{C} {'bf16' if bf16 else 'f32'}")
+    B.bsr_spmm(big[:, off:off + K], M, None, Yb[:, 3:3 + N])
+    X[:, :C] = 0.0
+    check_spmm(X, M, None, Yb[:, 3:3 + N], bf16=bf16)
+    assert bool((Yb[:, :3] == 7.0).all()) and bool((Yb[:, 3 + N:] == 7.0).all())
