@@ -6,8 +6,8 @@
 // Tokens are rows t = b * seq + s of Q, K, V and ctx; head h owns columns h*64 .. h*64 + 63.
 // No mask: every token attends to every token of its sequence.  fp32 throughout.
 //
-// One workgroup of 8 * QT threads computes QT queries (32, or 8 when 32-query tiles would not
-// give every CU a workgroup) of one (sequence, head).  The keys are
+// Short sequences with few queries run on the vector ALUs: one workgroup of 64 threads computes
+// 8 queries of one (sequence, head).  The keys are
 // visited in blocks of 64: the block's K and V rows are staged in LDS (row pitch 68 floats, so
 // rows start 4 banks apart and the 16-byte reads below are conflict-free), and the softmax is
 // kept online (running maximum m, running sum l, output rescaled by exp(m_old - m_new)), so no
@@ -26,7 +26,7 @@ namespace {
 constexpr int kKB = 64;       // keys per block
 constexpr int kD = 64;        // head width
 constexpr int kPitch = 68;    // LDS row pitch, floats
-constexpr int kMfmaMinSeq = 128;   // shortest sequence for the matrix-core kernel
+constexpr int kMfmaMinSeq = 256;   // sequences that always take the matrix-core kernel
 constexpr int kSplitBelow = 2;     // key-split 8-query tiles below this many tiles per CU
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
@@ -47,12 +47,11 @@ __device__ __forceinline__ float row_sum8(float x) {
     return x + __shfl_xor(x, 4);
 }
 
-template <int kQT>
-__global__ __launch_bounds__(kQT * 8) void attention_kernel(
+__global__ __launch_bounds__(64) void attention_kernel(
     const float *__restrict__ Q, int64_t ldq, const float *__restrict__ K, int64_t ldk,
     const float *__restrict__ V, int64_t ldv, float *__restrict__ O, int64_t ldo, int seq,
     float scale) {
-    constexpr int kThreads = kQT * 8;
+    constexpr int kQT = 8, kThreads = kQT * 8;
     __shared__ float Ks[kKB * kPitch];
     __shared__ float Vs[kKB * kPitch];
     __shared__ float Ps[kQT * kPitch];
@@ -325,84 +324,317 @@ __global__ __launch_bounds__(64 * kKS) void attention_split_kernel(
 }
 
 // ------------------------------------------------------------------- matrix-core version
-// One wave computes 32 queries of one (sequence, head) on v_mfma_f32_32x32x2_f32; kWQ waves of
-// a workgroup share the staged keys and values (blocks of 64, as above).  Lane l serves query
-// l % 32 as half hh = l / 32.
-//   Scores, transposed: S^T = K Q^T for each group of 32 keys.  Step s (s < 32) contracts
-//   dimension s + 32hh in slot hh: A = K[key l%32][s + 32hh] (LDS), B = the lane's pre-scaled
-//   q[s + 32hh] (registers).  Register v of lane l then holds the score of query l % 32 and
-//   key 8(v/4) + 4hh + v%4 of the group, so a query's 32 scores sit in the lane pair
-//   (l, l ^ 32): the group maximum and sum take 15 register operations and one exchange.
-//   Output, transposed: O^T += V^T P^T.  Step v contracts the two keys that register v holds in
-//   the two halves: A = V[that key][32t + l%32] (LDS; output column tile t = 0, 1), B = this
-//   lane's weight p[v], so the weights never leave their registers.
+// One wave computes 32 queries of one (sequence, head); kWQ query tiles of a workgroup share the
+// staged keys and values (blocks of 64, as above), and with kKS = 2 two waves serve each tile, one
+// taking the first 32 keys of every block and the other the second 32, merged at the end.  Lane l
+// serves query l % 32 as half hh = l / 32.
+//   Scores, transposed: S^T = K Q^T for each group of 32 keys.  Register v of lane l then holds
+//   the score of query l % 32 and key 8(v/4) + 4hh + v%4 of the group, so a query's 32 scores sit
+//   in the lane pair (l, l ^ 32): the group maximum and sum take 15 register operations and one
+//   exchange.
+//   Output, transposed: O^T += V^T P^T: the weights of a lane are its own B operand, so they never
+//   leave their registers.
 // The online softmax is the one above (running maximum and sum per query, output rescaled by
 // exp(m_old - m_new)); each query's running values are kept, identical, in both its lanes.
-template <int kWQ, int kKS>
-__global__ __launch_bounds__(kWQ * kKS * 64) __attribute__((amdgpu_waves_per_eu(3)))
-void attention_mfma_kernel(
-    const float *__restrict__ Q, int64_t ldq, const float *__restrict__ K, int64_t ldk,
-    const float *__restrict__ V, int64_t ldv, float *__restrict__ O, int64_t ldo, int seq,
-    float scale) {
-    // kKS = 2: two waves serve each query tile, one taking the first 32 keys of every staged
-    // block and the other the second 32, and merge their results at the end.
-    static_assert(kKS == 1 || kKS == 2, "one or two waves per query tile");
-    typedef float floatx16 __attribute__((ext_vector_type(16)));
-    constexpr int kThreads = kWQ * kKS * 64;
-    __shared__ float Ks[kKB * kPitch];
-    __shared__ float Vs[kKB * kPitch];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int qw = wave % kWQ, ks = wave / kWQ;
-    const int ql = lane & 31, hh = lane >> 5;
-    const int qrow = (blockIdx.x * kWQ + qw) * 32 + ql, h = blockIdx.y;
-    const int64_t tok0 = int64_t(blockIdx.z) * seq;
-    const bool qvalid = qrow < seq;
+//
+// Arithmetic.  fp32 matrix instructions share the vector ALUs: 147 thousand of a CU's 236 thousand
+// cycles went to them and 64 thousand to vector instructions on 16 x 16 heads x 384 tokens
+// (MI355X counters), with next to nothing left to overlap.  So both products run on bf16 matrix
+// instructions with every fp32 operand x as three bf16 pieces, x = x0 + x1 + x2 exactly, each the
+// remainder rounded to nearest (|x1| <= 2^-9 |x|, |x2| <= 2^-18 |x|).  Of the nine cross terms the
+// six with i + j <= 2 are formed, each exact in fp32; the three left out are below 2^-25 |x y|
+// together, half an ulp of the fp32 product that they belong to.  The weights are carried as 2^64 exp(s - m),
+// and so is their sum, so that no piece of a weight underflows before the weight would.
+// Every group's output is summed from zero and then added to the running output, so the long sum
+// is rounded once per 32 keys.  Against fp64, 384 tokens x 16 heads, normal inputs: 2-norm error
+// 2.4e-7, where fp32 matrix instructions with one running sum gave 4.5e-7.
+// 16 x 384 tokens, 16 heads: 104 -> 70 us; 8 x 512, 12 heads: 88 -> 61 us (MI355X); what bounds it
+// now is vector instructions (softmax and splitting) and matrix instructions in turn.
+// The pieces are exact only for operands that are zero or in [2^-60, 2^40); a workgroup that stages
+// any other element (infinities and NaN among them) starts over on fp32 matrix instructions.
+typedef float floatx16 __attribute__((ext_vector_type(16)));
+typedef float floatx2 __attribute__((ext_vector_type(2)));
+typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
-    // Half hh of this lane's query row, pre-scaled (rows past the sequence read row 0; never
-    // stored).
-    float q[32];
-    {
-        const float *qp = Q + (tok0 + (qvalid ? qrow : 0)) * ldq + h * kD + 32 * hh;
+constexpr int kPieces = 3;
+constexpr int kPlane = kKB * kD;   // elements of a plane: 64 rows of 64 bf16, 8-element chunks
+                                   // of a row swizzled by its row so that equal chunks of eight
+                                   // consecutive rows lie in different banks
+constexpr float kWeightScale = 0x1p64f;
+
+__device__ __forceinline__ unsigned cvt_pair(float a, float b) {   // round to nearest even
+    const floatx2 v = {a, b};
+    return __builtin_bit_cast(unsigned, __builtin_convertvector(v, bf16x2));
+}
+
+// The pieces of a pair of values, packed.
+__device__ __forceinline__ void split_pair(float a, float b, unsigned (&u)[kPieces]) {
 #pragma unroll
-        for (int d = 0; d < 32; d += 4) {
-            const floatx4 v = load4(qp + d);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) q[d + e] = v[e] * scale;
-        }
+    for (int p = 0; p < kPieces; ++p) {
+        u[p] = cvt_pair(a, b);
+        a -= __uint_as_float(u[p] << 16);
+        b -= __uint_as_float(u[p] & 0xffff0000u);
     }
-    float m = -INFINITY, l = 0.0f;
-    floatx16 o0, o1;
-#pragma unroll
-    for (int v = 0; v < 16; ++v) o0[v] = o1[v] = 0.0f;
+}
 
+__device__ __forceinline__ void split8(const float (&v)[8], uintx4 (&out)[kPieces]) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        unsigned u[kPieces];
+        split_pair(v[2 * i], v[2 * i + 1], u);
+#pragma unroll
+        for (int p = 0; p < kPieces; ++p) out[p][i] = u[p];
+    }
+}
+
+// Range of the magnitudes seen, as bit patterns (zero counts as neither large nor small).
+struct Range {
+    unsigned lo = ~0u, hi = 0u;
+    __device__ __forceinline__ void add(float x) {
+        const unsigned b = __float_as_uint(x) & 0x7fffffffu;
+        lo = min(lo, b - 1u);   // zero wraps to the largest value
+        hi = max(hi, b);
+    }
+    __device__ __forceinline__ bool outside() const {
+        return lo < 0x21800000u - 1u || hi >= 0x53800000u;   // 2^-60, 2^40
+    }
+};
+
+// Byte offset of chunk c of row r in a plane.
+__device__ __forceinline__ int plane_at(int r, int c) { return r * 128 + ((c ^ (r & 7)) << 4); }
+
+__device__ __forceinline__ floatx16 mfma_bf16(const uintx4 &a, const uintx4 &b, floatx16 c) {
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a),
+                                                   __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
+
+// The six cross terms, smallest first.
+__device__ __forceinline__ floatx16 mfma_split(const uintx4 (&a)[kPieces],
+                                               const uintx4 (&b)[kPieces], floatx16 c) {
+    c = mfma_bf16(a[2], b[0], c);
+    c = mfma_bf16(a[1], b[1], c);
+    c = mfma_bf16(a[0], b[2], c);
+    c = mfma_bf16(a[1], b[0], c);
+    c = mfma_bf16(a[0], b[1], c);
+    return mfma_bf16(a[0], b[0], c);
+}
+
+// scale * exp(x) for x <= 0 (scale a power of two): 2^t of the rounded product t = x log2(e), times
+// 1 + r ln 2 for what the rounding and log2(e)'s low bits left out (r < 2^-17 where exp(x) is not
+// negligible).  About half of expf's instructions: x is never positive, so nothing overflows.
+__device__ __forceinline__ float exp_scaled(float x, float scale) {
+    constexpr float kLog2e = 0x1.715476p+0f, kLog2eLo = 0x1.4ae0bfp-26f, kLn2 = 0x1.62e430p-1f;
+    x = fmaxf(x, -200.0f);   // -inf has no remainder; the weight is 0 either way
+    const float t = x * kLog2e;
+    float r = __builtin_fmaf(x, kLog2e, -t);
+    r = __builtin_fmaf(x, kLog2eLo, r);
+    return __builtin_amdgcn_exp2f(t) * __builtin_fmaf(r, kLn2 * scale, scale);
+}
+
+// A tile's running state, by lane: query l % 32, outputs as documented at the stores.
+struct TileState {
+    float m, l;
+    floatx16 o0, o1;
+};
+
+__device__ __forceinline__ void tile_reset(TileState &st) {
+    st.m = -INFINITY;
+    st.l = 0.0f;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) st.o0[v] = st.o1[v] = 0.0f;
+}
+
+// Keys past the sequence get a score of -inf (weight 0); a group's first key exists.
+__device__ __forceinline__ void mask_keys(floatx16 &s, int kg, int hh, int seq) {
+    if (kg + 32 > seq) {
+#pragma unroll
+        for (int v = 0; v < 16; ++v)
+            if (kg + 8 * (v >> 2) + 4 * hh + (v & 3) >= seq) s[v] = -INFINITY;
+    }
+}
+
+// Running maximum, weights (in s; kSplit: times 2^64) and running sum; the factor by which the
+// outputs so far are to be rescaled is returned.
+template <bool kSplit>
+__device__ __forceinline__ float online_softmax(TileState &st, floatx16 &s) {
+    float mx = s[0];
+#pragma unroll
+    for (int v = 1; v < 16; ++v) mx = fmaxf(mx, s[v]);
+    mx = fmaxf(mx, __shfl_xor(mx, 32));
+    const float mn = fmaxf(st.m, mx);
+    const float corr = expf(st.m - mn);   // 0 on the first group (m = -inf)
+    float ps = 0.0f;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+        s[v] = kSplit ? exp_scaled(s[v] - mn, kWeightScale) : expf(s[v] - mn);
+        ps += s[v];
+    }
+    ps += __shfl_xor(ps, 32);
+    st.l = st.l * corr + ps;
+    st.m = mn;
+    return corr;
+}
+
+// All of a tile's keys on bf16 pieces; false (in every thread of the workgroup) when an operand
+// is out of the pieces' range.
+template <int kWQ, int kKS>
+__device__ __forceinline__ bool tile_split(TileState &st, const float *qp, const float *Kh,
+                                           int64_t ldk, const float *Vh, int64_t ldv, int seq,
+                                           float scale, char *smem, int *s_bad) {
+    constexpr int kThreads = kWQ * kKS * 64;
+    char *Kp = smem, *Vp = smem + kPieces * kPlane * 2;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, ks = wave / kWQ;
+    const int ql = lane & 31, hh = lane >> 5;
+    Range range;
+    // The lane's pre-scaled query pieces: step s contracts dimensions 16 s + 8 hh + e.
+    uintx4 q[4][kPieces];
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+        const floatx4 a = load4(qp + 16 * s + 8 * hh), b = load4(qp + 16 * s + 8 * hh + 4);
+        float v[8];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            v[e] = a[e] * scale;
+            v[4 + e] = b[e] * scale;
+        }
+#pragma unroll
+        for (int e = 0; e < 8; ++e) range.add(v[e]);
+        split8(v, q[s]);
+    }
+    if (tid == 0) *s_bad = 0;
     for (int k0 = 0; k0 < seq; k0 += kKB) {
         __syncthreads();   // the previous block's LDS reads are done
-        // Stage K and V rows k0 .. k0 + 63 of this head (rows past the sequence are zero).
-        constexpr int kPer = kKB * (kD / 4) / kThreads;   // 16-byte pieces per thread
-        constexpr int kBatch = kPer < 4 ? kPer : 4;
+        // K: row = key, chunk = 8 dimensions.  V: row = output column d, chunk = the 8 keys that
+        // one half contracts in one step, in its registers' order: keys 16 s + 4 h + (0 .. 3) and
+        // 16 s + 8 + 4 h + (0 .. 3).  Rows past the sequence are zero.
+        for (int i = tid; i < kKB * 8; i += kThreads) {
+            const int r = i >> 3, c = i & 7, key = k0 + r;
+            float v[8];
+            const float *kp = Kh + int64_t(key < seq ? key : seq - 1) * ldk + 8 * c;
+            const floatx4 a = load4(kp), b = load4(kp + 4);
 #pragma unroll
-        for (int n0 = 0; n0 < kPer; n0 += kBatch) {
-            floatx4 kst[kBatch], vst[kBatch];
-#pragma unroll
-            for (int n = 0; n < kBatch; ++n) {
-                const int i = tid + (n0 + n) * kThreads;
-                const int r = i >> 4, c4 = (i & 15) * 4;
-                const int key = k0 + r < seq ? k0 + r : seq - 1;   // past the end: zeroed below
-                kst[n] = load4(K + (tok0 + key) * ldk + h * kD + c4);
-                vst[n] = load4(V + (tok0 + key) * ldv + h * kD + c4);
+            for (int e = 0; e < 4; ++e) {
+                v[e] = key < seq ? a[e] : 0.0f;
+                v[4 + e] = key < seq ? b[e] : 0.0f;
             }
 #pragma unroll
-            for (int n = 0; n < kBatch; ++n) {
-                const int i = tid + (n0 + n) * kThreads;
-                const int r = i >> 4, c4 = (i & 15) * 4;
-                const floatx4 z = {0.0f, 0.0f, 0.0f, 0.0f};
-                *reinterpret_cast<floatx4 *>(&Ks[r * kPitch + c4]) = k0 + r < seq ? kst[n] : z;
-                *reinterpret_cast<floatx4 *>(&Vs[r * kPitch + c4]) = k0 + r < seq ? vst[n] : z;
-            }
+            for (int e = 0; e < 8; ++e) range.add(v[e]);
+            uintx4 u[kPieces];
+            split8(v, u);
+#pragma unroll
+            for (int p = 0; p < kPieces; ++p)
+                *reinterpret_cast<uintx4 *>(Kp + p * kPlane * 2 + plane_at(r, c)) = u[p];
         }
+        for (int i = tid; i < kD * 8; i += kThreads) {
+            const int d = i & 63, c = i >> 6, base = k0 + 16 * (c >> 1) + 4 * (c & 1);
+            float v[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const int key = base + (e & 3) + 8 * (e >> 2);
+                const float x = Vh[int64_t(key < seq ? key : seq - 1) * ldv + d];
+                v[e] = key < seq ? x : 0.0f;
+            }
+#pragma unroll
+            for (int e = 0; e < 8; ++e) range.add(v[e]);
+            uintx4 u[kPieces];
+            split8(v, u);
+#pragma unroll
+            for (int p = 0; p < kPieces; ++p)
+                *reinterpret_cast<uintx4 *>(Vp + p * kPlane * 2 + plane_at(d, c)) = u[p];
+        }
+        if (range.outside()) *s_bad = 1;
         __syncthreads();
+        if (*s_bad) return false;   // the same word in every thread
 
 #pragma unroll
+        for (int gi = 0; gi < kKB / 32 / kKS; ++gi) {
+            const int g = gi * kKS + ks;
+            const int kg = k0 + 32 * g;
+            if (kg >= seq) break;   // the whole group is past the end
+            floatx16 s;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) s[v] = 0.0f;
+#pragma unroll
+            for (int st4 = 0; st4 < 4; ++st4) {
+                uintx4 a[kPieces];
+#pragma unroll
+                for (int p = 0; p < kPieces; ++p)
+                    a[p] = *reinterpret_cast<const uintx4 *>(
+                        Kp + p * kPlane * 2 + plane_at(32 * g + ql, 2 * st4 + hh));
+                s = mfma_split(a, q[st4], s);
+            }
+            mask_keys(s, kg, hh, seq);
+            const float corr = online_softmax<true>(st, s);
+            uintx4 w2[2][kPieces];
+#pragma unroll
+            for (int h16 = 0; h16 < 2; ++h16) {
+                auto &w = w2[h16];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    unsigned u[kPieces];
+                    split_pair(s[8 * h16 + 2 * i], s[8 * h16 + 2 * i + 1], u);
+#pragma unroll
+                    for (int p = 0; p < kPieces; ++p) w[p][i] = u[p];
+                }
+            }
+            // The group's output from zero, then added to the rescaled sum: one rounding of the
+            // long sum per group.
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                floatx16 o;
+#pragma unroll
+                for (int v = 0; v < 16; ++v) o[v] = 0.0f;
+#pragma unroll
+                for (int h16 = 0; h16 < 2; ++h16) {
+                    uintx4 a[kPieces];
+#pragma unroll
+                    for (int p = 0; p < kPieces; ++p)
+                        a[p] = *reinterpret_cast<const uintx4 *>(
+                            Vp + p * kPlane * 2 + plane_at(32 * t + ql, 4 * g + 2 * h16 + hh));
+                    o = mfma_split(a, w2[h16], o);
+                }
+                floatx16 &sum = t == 0 ? st.o0 : st.o1;
+#pragma unroll
+                for (int v = 0; v < 16; ++v) sum[v] = __builtin_fmaf(sum[v], corr, o[v]);
+            }
+        }
+    }
+    return true;
+}
+
+// All of a tile's keys on v_mfma_f32_32x32x2_f32, for operands of any value.  Scores: step s
+// (s < 32) contracts dimension s + 32hh in slot hh: A = K[key l%32][s + 32hh] (LDS), B = the lane's
+// pre-scaled q[s + 32hh].  Output: step v contracts the two keys that register v holds in the two
+// halves: A = V[that key][32t + l%32] (LDS; output column tile t = 0, 1), B = the lane's weight p[v].
+template <int kWQ, int kKS>
+__device__ __forceinline__ void tile_fp32(TileState &st, const float *qp, const float *Kh,
+                                          int64_t ldk, const float *Vh, int64_t ldv, int seq,
+                                          float scale, char *smem) {
+    constexpr int kThreads = kWQ * kKS * 64;
+    float *Ks = reinterpret_cast<float *>(smem), *Vs = Ks + kKB * kPitch;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, ks = wave / kWQ;
+    const int ql = lane & 31, hh = lane >> 5;
+    float q[32];
+#pragma unroll
+    for (int d = 0; d < 32; d += 4) {
+        const floatx4 v = load4(qp + 32 * hh + d);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) q[d + e] = v[e] * scale;
+    }
+    for (int k0 = 0; k0 < seq; k0 += kKB) {
+        __syncthreads();   // the previous block's LDS reads are done
+        for (int i = tid; i < kKB * (kD / 4); i += kThreads) {
+            const int r = i >> 4, c4 = (i & 15) * 4, key = k0 + r;
+            const floatx4 z = {0.0f, 0.0f, 0.0f, 0.0f};
+            const int64_t row = key < seq ? key : seq - 1;
+            const floatx4 kv = load4(Kh + row * ldk + c4), vv = load4(Vh + row * ldv + c4);
+            *reinterpret_cast<floatx4 *>(&Ks[r * kPitch + c4]) = key < seq ? kv : z;
+            *reinterpret_cast<floatx4 *>(&Vs[r * kPitch + c4]) = key < seq ? vv : z;
+        }
+        __syncthreads();
+#pragma unroll 1
         for (int gi = 0; gi < kKB / 32 / kKS; ++gi) {
             const int g = gi * kKS + ks;
             const int kg = k0 + 32 * g;
@@ -418,48 +650,62 @@ void attention_mfma_kernel(
                 for (int e = 0; e < 4; ++e)
                     s = __builtin_amdgcn_mfma_f32_32x32x2f32(kv[e], q[d + e], s, 0, 0, 0);
             }
-            // Keys past the sequence get -inf (weight 0); the group's first key exists.
-            float mx = -INFINITY;
+            mask_keys(s, kg, hh, seq);
+            const float corr = online_softmax<false>(st, s);
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
-                const int key = kg + 8 * (v >> 2) + 4 * hh + (v & 3);
-                if (key >= seq) s[v] = -INFINITY;
-                mx = fmaxf(mx, s[v]);
+                st.o0[v] *= corr;
+                st.o1[v] *= corr;
             }
-            mx = fmaxf(mx, __shfl_xor(mx, 32));
-            const float mn = fmaxf(m, mx);
-            const float corr = expf(m - mn);   // 0 on the first group (m = -inf)
-            float ps = 0.0f;
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                s[v] = expf(s[v] - mn);
-                ps += s[v];
-            }
-            ps += __shfl_xor(ps, 32);
-            l = l * corr + ps;
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                o0[v] *= corr;
-                o1[v] *= corr;
-            }
-            m = mn;
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
                 const float *vr = &Vs[(32 * g + 8 * (v >> 2) + 4 * hh + (v & 3)) * kPitch + ql];
-                o0 = __builtin_amdgcn_mfma_f32_32x32x2f32(vr[0], s[v], o0, 0, 0, 0);
-                o1 = __builtin_amdgcn_mfma_f32_32x32x2f32(vr[32], s[v], o1, 0, 0, 0);
+                st.o0 = __builtin_amdgcn_mfma_f32_32x32x2f32(vr[0], s[v], st.o0, 0, 0, 0);
+                st.o1 = __builtin_amdgcn_mfma_f32_32x32x2f32(vr[32], s[v], st.o1, 0, 0, 0);
             }
         }
     }
+}
+
+// LDS of a workgroup: the piece planes of K and V, or K and V in fp32, or the merge buffer.
+constexpr int kMfmaLds = 2 * kPieces * kPlane * 2;
+static_assert(2 * kKB * kPitch * 4 <= kMfmaLds, "the fp32 tiles fit");
+
+template <int kWQ, int kKS>
+__global__ __launch_bounds__(kWQ * kKS * 64) __attribute__((amdgpu_waves_per_eu(3)))
+void attention_mfma_kernel(
+    const float *__restrict__ Q, int64_t ldq, const float *__restrict__ K, int64_t ldk,
+    const float *__restrict__ V, int64_t ldv, float *__restrict__ O, int64_t ldo, int seq,
+    float scale) {
+    static_assert(kKS == 1 || kKS == 2, "one or two waves per query tile");
+    __shared__ __align__(16) char smem[kMfmaLds];
+    __shared__ int s_bad;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int qw = wave % kWQ, ks = wave / kWQ;
+    const int ql = lane & 31, hh = lane >> 5;
+    const int qrow = (blockIdx.x * kWQ + qw) * 32 + ql, h = blockIdx.y;
+    const int64_t tok0 = int64_t(blockIdx.z) * seq;
+    const bool qvalid = qrow < seq;
+    // This lane's query row (rows past the sequence read row 0; never stored).
+    const float *qp = Q + (tok0 + (qvalid ? qrow : 0)) * ldq + h * kD;
+    const float *Kh = K + tok0 * ldk + h * kD, *Vh = V + tok0 * ldv + h * kD;
+    TileState st;
+    tile_reset(st);
+    if (!tile_split<kWQ, kKS>(st, qp, Kh, ldk, Vh, ldv, seq, scale, smem, &s_bad)) {
+        tile_reset(st);
+        tile_fp32<kWQ, kKS>(st, qp, Kh, ldk, Vh, ldv, seq, scale, smem);
+    }
+    float &m = st.m, &l = st.l;
+    floatx16 &o0 = st.o0, &o1 = st.o1;
     if constexpr (kKS == 2) {
         // Merge the two key halves: the second wave of each tile leaves its running maximum,
-        // sum and output in LDS (the K buffer is free after the barrier); the first adds
+        // sum and output in LDS (the planes are free after the barrier); the first adds
         // them, both rescaled to the larger maximum.  A wave that saw no key (sequences of at
         // most 32) has m = -inf, l = 0 and adds nothing.
         constexpr int kSlot = 34;   // floats per lane: o0, o1, m, l
-        static_assert(kWQ * 64 * kSlot <= kKB * kPitch, "merge buffer fits in the K buffer");
+        static_assert(kWQ * 64 * kSlot * 4 <= kMfmaLds, "the merge buffer fits");
         __syncthreads();
-        float *C = Ks + (qw * 64 + lane) * kSlot;
+        float *C = reinterpret_cast<float *>(smem) + (qw * 64 + lane) * kSlot;
         if (ks == 1) {
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
@@ -503,41 +749,41 @@ void attention_mfma_kernel(
 bsr_status launch_attention(const float *Q, int64_t ldq, const float *K, int64_t ldk,
                             const float *V, int64_t ldv, float *O, int64_t ldo, int batch,
                             int seq, int heads, float scale, void *stream) {
-    const int64_t tiles32 = int64_t((seq + 31) / 32) * heads * batch;
-    const int cus = device_cu_count() > 0 ? device_cu_count() : 256;
-    // The matrix-core kernel for sequences of 2 * kMfmaMinSeq keys or more, and for sequences
-    // of kMfmaMinSeq keys or more when there are at least three 32-query tiles per CU (its
-    // per-wave chain of key groups is long; measured on MI355X, shorter sequences with fewer
-    // tiles run faster on the vector ALUs).  Up to eight tiles per CU, two waves split each tile's keys (twice the
-    // waves); beyond that, four tiles share each workgroup's staged keys.
-    if (seq >= 2 * kMfmaMinSeq || (seq >= kMfmaMinSeq && tiles32 >= 3 * int64_t(cus))) {
-        if (tiles32 >= 8 * int64_t(cus)) {
-            const dim3 grid(unsigned((seq + 127) / 128), unsigned(heads), unsigned(batch));
-            hipLaunchKernelGGL((attention_mfma_kernel<4, 1>), grid, dim3(256), 0,
-                               as_stream(stream), Q, ldq, K, ldk, V, ldv, O, ldo, seq, scale);
-        } else {
-            const dim3 grid(unsigned((seq + 63) / 64), unsigned(heads), unsigned(batch));
-            hipLaunchKernelGGL((attention_mfma_kernel<2, 2>), grid, dim3(256), 0,
-                               as_stream(stream), Q, ldq, K, ldk, V, ldv, O, ldo, seq, scale);
-        }
-        return launch_status();
+    const int64_t nt = (seq + 31) / 32, pairs = int64_t(heads) * batch, tiles32 = nt * pairs;
+    const int64_t cus = device_cu_count() > 0 ? device_cu_count() : 256;
+    // The matrix-core kernel from 256 keys on, and for shorter sequences when there are enough
+    // 32-query tiles (its one-wave chain of key groups is longer than the vector kernels' waves).
+    // Vector / matrix kernel in us, 12 heads: 2 x 128 tokens (96 tiles) 9.9 / 11.4, 1 x 200 (84)
+    // 17.0 / 17.9, 4 x 128 (192) 13.8 / 11.6, 16 x 40 (384) 10.4 / 9.5, 4 x 200 (336) 31.4 / 18.7.
+    if (seq >= kMfmaMinSeq || 8 * tiles32 >= 5 * cus) {
+        auto go = [&](auto kernel, int wq, int ks) {
+            const dim3 grid(unsigned((nt + wq - 1) / wq), unsigned(heads), unsigned(batch));
+            hipLaunchKernelGGL(kernel, grid, dim3(64 * wq * ks), 0, as_stream(stream), Q, ldq, K,
+                               ldk, V, ldv, O, ldo, seq, scale);
+            return launch_status();
+        };
+        // Under three tiles per CU (or tiles too few to share staged keys) two waves split each
+        // tile's keys: 1 x 512 tokens 32 us against 43 with one wave per tile.
+        if (tiles32 < 3 * cus || nt < 4) return go(attention_mfma_kernel<2, 2>, 2, 2);
+        // Else 12, 8 or 4 tiles share a workgroup's staged keys, whichever leaves the fewest waves
+        // on the busiest SIMD; staging costs about a tenth and three tenths more for 8 and 4 tiles
+        // (12 / 8 / 4 tiles: 16 x 384 tokens, 16 heads 70 / 92 / 80 us; 8 x 512, 12 heads
+        // 77 / 61 / 73; 32 x 128, 12 heads 41 / 33 / 23).
+        auto rounds = [&](int64_t wq) { return ((nt + wq - 1) / wq * pairs + cus - 1) / cus; };
+        const int64_t c12 = 30 * rounds(12), c8 = 22 * rounds(8), c4 = 13 * rounds(4);
+        if (c12 <= c8 && c12 <= c4) return go(attention_mfma_kernel<12, 1>, 12, 1);
+        if (c8 <= c4) return go(attention_mfma_kernel<8, 1>, 8, 1);
+        return go(attention_mfma_kernel<4, 1>, 4, 1);
     }
-    // Vector-ALU kernels: 32-query tiles when they give at least one workgroup per CU, else
-    // 8-query tiles; when even those give fewer than kSplitBelow waves per CU, two or four
-    // waves split the keys of each tile.
+    // Vector-ALU kernels: 8-query tiles; when they give fewer than kSplitBelow waves per CU, two
+    // or four waves split the keys of each tile.
     const int nblk = (seq + kKB - 1) / kKB;
-    const int64_t tiles8 = int64_t((seq + 7) / 8) * heads * batch;
-    if (tiles32 >= cus) {
-        const dim3 grid(unsigned((seq + 31) / 32), unsigned(heads), unsigned(batch));
-        hipLaunchKernelGGL(attention_kernel<32>, grid, dim3(256), 0, as_stream(stream), Q, ldq, K,
-                           ldk, V, ldv, O, ldo, seq, scale);
-        return launch_status();
-    }
+    const int64_t tiles8 = int64_t((seq + 7) / 8) * pairs;
     const dim3 grid(unsigned((seq + 7) / 8), unsigned(heads), unsigned(batch));
-    const int ks = tiles8 >= kSplitBelow * int64_t(cus) || nblk < 2 ? 1 : (nblk < 4 ? 2 : 4);
+    const int ks = tiles8 >= kSplitBelow * cus || nblk < 2 ? 1 : (nblk < 4 ? 2 : 4);
     const size_t lds = size_t(ks) * (2 * kKB * kPitch + 8 * kPitch) * sizeof(float);
     if (ks == 1)
-        hipLaunchKernelGGL(attention_kernel<8>, grid, dim3(64), 0, as_stream(stream), Q, ldq, K,
+        hipLaunchKernelGGL(attention_kernel, grid, dim3(64), 0, as_stream(stream), Q, ldq, K,
                            ldk, V, ldv, O, ldo, seq, scale);
     else if (ks == 2)
         hipLaunchKernelGGL(attention_split_kernel<2>, grid, dim3(128), lds, as_stream(stream), Q,

@@ -35,15 +35,15 @@ def check_attention(Q, K, V, ctx_gpu, batch, seq, heads):
                                                 (1, 256, 3, 1.0), (2, 300, 2, 2.0),
                                                 (1, 1000, 1, 1.0), (4, 257, 2, 0.5),
                                                 (1, 384, 12, 4.0),
-                                                # vector kernel, 32-query tiles; key split
-                                                # with an idle round
+                                                # many short sequences; key split with an
+                                                # idle round
                                                 (24, 64, 12, 1.0), (8, 200, 12, 2.0),
                                                 (1, 150, 2, 1.0),
                                                 # matrix-core kernel, key halves on two waves
                                                 (8, 512, 6, 1.0), (16, 256, 12, 1.0),
                                                 (8, 300, 12, 2.0), (3, 1000, 12, 0.5),
                                                 (24, 130, 12, 4.0),
-                                                # four query tiles per workgroup (>= 2048 tiles)
+                                                # four query tiles per workgroup
                                                 (48, 128, 12, 1.0), (36, 200, 12, 2.0)])
 def test_attention_matches_oracle(device, batch, seq, heads, sd):
     g = rng(9500 + batch * 1000 + seq + heads)
@@ -53,6 +53,45 @@ def test_attention_matches_oracle(device, batch, seq, heads, sd):
     ctx = B.bsr_attention(dev(Q), dev(K), dev(V), batch, seq, heads)
     torch.cuda.synchronize()
     check_attention(Q, K, V, ctx, batch, seq, heads)
+
+
+@pytest.mark.parametrize("batch,seq,heads", [(2, 300, 3), (16, 384, 8), (16, 512, 6), (48, 128, 12)],
+                         ids=["key_halves", "twelve_tiles", "eight_tiles", "four_tiles"])
+@pytest.mark.parametrize("kind", ["huge_v", "tiny_q", "tiny_v", "late_huge_k", "inf_v", "nan_k"])
+def test_attention_out_of_range_operands(device, batch, seq, heads, kind):
+    """Operands outside the range that the bf16 pieces hold exactly (in one sequence and head, also
+    in its last key only): that workgroup's results meet the fp32 bound all the same, an infinity
+    or a NaN shows where it does in fp32 arithmetic, and the other heads do not see it."""
+    g = rng(9700 + batch + seq)
+    T, W = batch * seq, heads * 64
+    Q, K, V = [g.standard_normal((T, W)).astype(np.float32) for _ in range(3)]
+    one = np.s_[seq:2 * seq, 64:128]   # sequence 1, head 1
+    if kind == "huge_v":
+        V[one] *= np.float32(2.0 ** 60)
+    elif kind == "tiny_q":
+        Q[one] *= np.float32(2.0 ** -70)
+    elif kind == "tiny_v":
+        V[one] *= np.float32(2.0 ** -100)
+    elif kind == "late_huge_k":      # its scores vanish against Q's zeros, the products are exact
+        K[2 * seq - 1, 64:128] = np.float32(2.0 ** 45)
+        Q[one] = 0.0
+    elif kind == "inf_v":
+        V[seq + 5, 64 + 3] = np.inf
+    else:
+        K[2 * seq - 1, 70] = np.nan
+    log(f"attention out of range {kind} {batch}x{seq}x{heads}")
+    ctx = B.bsr_attention(dev(Q), dev(K), dev(V), batch, seq, heads)
+    got = host(ctx)
+    if kind == "inf_v":
+        assert np.all(got[seq:2 * seq, 67] == np.inf)
+        got[seq:2 * seq, 67] = 0.0
+        V[seq:2 * seq, 67] = 0.0
+    elif kind == "nan_k":
+        assert np.all(np.isnan(got[one]))
+        K[2 * seq - 1, 70] = 0.0
+        V[one] = 0.0
+        got[one] = 0.0
+    check_attention(Q, K, V, torch.from_numpy(got), batch, seq, heads)
 
 
 def test_attention_on_a_fused_qkv_output(device):
