@@ -16,6 +16,8 @@ _HERE = os.path.dirname(os.path.abspath(__file__))
 LIBRARY = os.path.join(_HERE, "libbsr.so")
 
 BSR_F32, BSR_BF16 = 0, 1
+_I32, _F32 = torch.int32, torch.float32
+_DATA_DTYPES = (torch.float32, torch.bfloat16)
 STATUS = {0: "BSR_OK", 1: "BSR_ERR_NULL", 2: "BSR_ERR_SHAPE", 3: "BSR_ERR_ARG",
           4: "BSR_ERR_DTYPE", 5: "BSR_ERR_CAPACITY", 6: "BSR_ERR_WORKSPACE", 7: "BSR_ERR_HIP",
           8: "BSR_ERR_ARCH", 9: "BSR_ERR_UNSUPPORTED"}
@@ -191,6 +193,11 @@ def _require_cuda(t: torch.Tensor, name: str, dtype=None) -> None:
 
 def _pitch(t: torch.Tensor, name: str) -> int:
     """Row pitch (elements) of a 2-D tensor whose rows are contiguous."""
+    shape = t.shape
+    if len(shape) == 2 and shape[0] > 1 and shape[1] > 1:
+        row, col = t.stride()
+        if col == 1:
+            return row
     if t.dim() == 2 and t.numel() == 0:
         return max(t.shape[1], 1)          # an empty tensor's strides carry no layout
     if t.dim() != 2 or (t.shape[1] > 1 and t.stride(1) != 1):
@@ -218,6 +225,19 @@ class BSRMatrix:
         """Raise unless the tensors hold the arrays the descriptor names (the C side cannot see
         a tensor's size): indptr int32 with at least N/R + 1 entries, indices int32 with at
         least nnzb, data [>= nnzb, R, C] float32 or bfloat16, each contiguous on a GPU."""
+        # One pass over the conditions; anything unexpected goes through them one by one below,
+        # for the error that names it.
+        R, C, ip, ix, d, k = self.R, self.C, self.indptr, self.indices, self.data, self.nnzb
+        if (R > 0 and C > 0 and not self.n_rows % R and not self.n_cols % C
+                and isinstance(ip, torch.Tensor) and isinstance(ix, torch.Tensor)
+                and isinstance(d, torch.Tensor)
+                and ip.dtype == _I32 and ix.dtype == _I32 and d.dtype in _DATA_DTYPES
+                and ip.is_cuda and ix.is_cuda and d.is_cuda
+                and ip.is_contiguous() and ix.is_contiguous() and d.is_contiguous()
+                and ip.numel() > self.n_rows // R and ix.numel() >= k):
+            shape = d.shape
+            if len(shape) == 3 and shape[1] == R and shape[2] == C and shape[0] >= k:
+                return
         if self.R <= 0 or self.C <= 0 or self.n_rows % self.R or self.n_cols % self.C:
             raise ValueError(f"block {self.R}x{self.C} does not tile {self.n_rows}x{self.n_cols}")
         nb_rows = self.n_rows // self.R
@@ -240,6 +260,10 @@ class BSRMatrix:
 
     def struct(self) -> bsr_matrix_t:
         self.check()
+        return self._descriptor()
+
+    def _descriptor(self) -> bsr_matrix_t:
+        """The C descriptor, for a caller that has just called check()."""
         return bsr_matrix_t(self.n_rows, self.n_cols, self.R, self.C, self.nnzb,
                             _ptr(self.indptr), _ptr(self.indices), _ptr(self.data), self.dtype)
 
@@ -349,13 +373,13 @@ def bsr_spmm_ex(X: torch.Tensor, W: BSRMatrix, bias: torch.Tensor | None = None,
                 slices: int | None = None, stream=None) -> torch.Tensor:
     """bsr_spmm with an explicit kernel (KERNEL_*) and slice count; None = automatic."""
     if Y is None and isinstance(X, torch.Tensor) and X.dim() == 2:
-        Y = torch.empty((X.shape[0], W.n_rows), dtype=torch.float32, device=X.device)
+        Y = X.new_empty((X.shape[0], W.n_rows), dtype=_F32)
     _check_call(X, W, bias, Y)
     x_dtype = BSR_BF16 if X.dtype == torch.bfloat16 else BSR_F32
     T = X.shape[0]
     ldx = _pitch(X, "X")
     ldy = _pitch(Y, "Y")
-    m = W.struct()
+    m = W._descriptor()   # _check_call has checked W
     if kernel is None and slices is None:
         _check(_lib().bsr_spmm(_ptr(X), x_dtype, T, ldx, ctypes.byref(m), _ptr(bias), _ptr(Y),
                                ldy, _stream(stream)), "bsr_spmm")
@@ -371,6 +395,17 @@ def _check_call(X: torch.Tensor, W: BSRMatrix, bias: torch.Tensor | None,
                 Y: torch.Tensor) -> None:
     """Shapes before anything reaches the library: X is [T, K] and Y [T, N] with K, N the
     matrix's, so every row the kernels read or write lies inside its tensor; then devices."""
+    if isinstance(X, torch.Tensor) and isinstance(Y, torch.Tensor):
+        # One pass over the conditions, as in BSRMatrix.check.
+        xs, ys = X.shape, Y.shape
+        if (len(xs) == 2 and xs[1] == W.n_cols and len(ys) == 2 and ys[0] == xs[0]
+                and ys[1] == W.n_rows and X.dtype in _DATA_DTYPES and Y.dtype == _F32
+                and X.is_cuda and Y.is_cuda
+                and (bias is None or (isinstance(bias, torch.Tensor) and bias.dtype == _F32
+                                      and bias.is_cuda and bias.dim() == 1
+                                      and bias.numel() == W.n_rows and bias.is_contiguous()))):
+            W.check()
+            return
     if not isinstance(X, torch.Tensor) or X.dim() != 2 or X.shape[1] != W.n_cols:
         raise ValueError(f"X must be [T, {W.n_cols}]")
     if not isinstance(Y, torch.Tensor) or tuple(Y.shape) != (X.shape[0], W.n_rows):
@@ -458,7 +493,7 @@ class SpmmBatchCall:
         items = (bsr_spmm_item_t * max(len(products), 1))()
         for i, (X, W, bias, Y) in enumerate(products):
             _check_call(X, W, bias, Y)
-            m = W.struct()
+            m = W._descriptor()
             self._mats.append(m)
             items[i] = bsr_spmm_item_t(_ptr(X), BSR_BF16 if X.dtype == torch.bfloat16 else BSR_F32,
                                        X.shape[0], _pitch(X, "X"), ctypes.pointer(m), _ptr(bias),
