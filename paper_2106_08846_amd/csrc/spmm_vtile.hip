@@ -189,20 +189,24 @@ struct DOps {
     float w[DShape<R, C>::NWV];   // word 16 k + lane % 16 of the half's chunk
 };
 
-// The chunk that starts `o` blocks into the row (ranges and offsets as in vload: past the
-// row's end a load returns 0 and touches no memory).  Lane l reads word 16 k + l % 16 of the
-// chunk's weights and column l % 16 of its blocks; lanes past the chunk read the next blocks'
-// words, which no broadcast selects.
+// Iteration `it` of a row: blocks 2 U it .. 2 U (it + 1) - 1, half h holding the blocks of its
+// parity (slot u: block 2 u + h), so that a short row is split evenly between the halves (with U
+// consecutive blocks per half a row of two 1x32 blocks ran on one half).  Ranges as in vload: past
+// the row's end a load returns 0 and touches no memory.  Lane l reads word 16 k + l % 16 of its
+// half's weights and the column of slot l % 16; lanes past the chunk read words that no broadcast
+// selects.
 template <int R, int C>
 __device__ __forceinline__ void dload(DOps<R, C> &ops, __amdgpu_buffer_rsrc_t ri,
-                                      __amdgpu_buffer_rsrc_t rd, int o) {
+                                      __amdgpu_buffer_rsrc_t rd, int it) {
     using S = DShape<R, C>;
-    const int i = threadIdx.x & 15;
-    ops.j = int(__builtin_amdgcn_raw_buffer_load_b32(ri, (o + i) * 4, 0, 0));
+    const int i = threadIdx.x & 15, h = (threadIdx.x & 63) >> 5, base = uniform(2 * it * S::U);
+    ops.j = int(__builtin_amdgcn_raw_buffer_load_b32(ri, (2 * i + h) * 4, base * 4, 0));
 #pragma unroll
-    for (int k = 0; k < DShape<R, C>::NWV; ++k)
-        ops.w[k] = __uint_as_float(
-            __builtin_amdgcn_raw_buffer_load_b32(rd, (o * S::RC + 16 * k + i) * 4, 0, 0));
+    for (int k = 0; k < DShape<R, C>::NWV; ++k) {
+        const int word = 16 * k + i, u = word / S::RC;
+        ops.w[k] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(
+            rd, ((u + h) * S::RC + word) * 4, base * (S::RC * 4), 0));
+    }
 }
 
 // acc += w * x with w the value of lane L (0 .. 15, a constant once the caller's loops are
@@ -343,9 +347,16 @@ using OpsOf = std::conditional_t<BF, VOps<R, C>, DOps<R, C>>;
 
 template <int R, int C, bool BF>
 __device__ __forceinline__ void oload(OpsOf<R, C, BF> &ops, __amdgpu_buffer_rsrc_t ri,
-                                      __amdgpu_buffer_rsrc_t rd, int o) {
-    if constexpr (BF) vload<R, C, BF>(ops, ri, rd, o);
-    else dload<R, C>(ops, ri, rd, o);
+                                      __amdgpu_buffer_rsrc_t rd, int it, int h) {
+    if constexpr (BF) vload<R, C, BF>(ops, ri, rd, (2 * it + h) * VShape<R, C>::U);
+    else dload<R, C>(ops, ri, rd, it);
+}
+
+// Blocks of half h in iteration `it` of a row of m blocks.
+template <int R, int C, bool BF>
+__device__ __forceinline__ int half_blocks(int m, int it, int h) {
+    if constexpr (BF) return m - (2 * it + h) * VShape<R, C>::U;
+    else return (m - 2 * it * DShape<R, C>::U - h + 1) >> 1;
 }
 
 template <int R, int C, bool BF, bool MASKED>
@@ -416,7 +427,7 @@ __device__ __forceinline__ void stream_rows(int row0, int row_hi, int step,
         auto load_next = [&](DOps<R, C> &o) {
             // Iteration il of row kl (nothing once the group is done), then advance.
             if (kl < nr) {
-                dload<R, C>(o, ri, rd, (2 * il + h) * U);
+                dload<R, C>(o, ri, rd, il);
                 if (++il == lits) {
                     il = 0;
                     if (++kl < nr) open_row();
@@ -445,7 +456,7 @@ __device__ __forceinline__ void stream_rows(int row0, int row_hi, int step,
 #pragma unroll
             for (int ph = 0; ph < kDD; ++ph) {
                 if (kc < nr) {
-                    const int nv = cm - (2 * ic + h) * U;
+                    const int nv = half_blocks<R, C, false>(cm, ic, h);
                     if (ic + 1 == cits) {
                         dcompute<R, C, true>(acc, ring[ph], xrow, Kb, nv);
                         // Row kc is complete: sum the halves (as in the row loop) and store.
@@ -602,22 +613,22 @@ __global__ __launch_bounds__((kWaves<R, C, BF> * 64)) void spmm_vtile_kernel(con
             // for the current chunk always leaves the next one's loads in flight (a conditional
             // load left the compiler's wait at zero outstanding loads).
             OpsOf<R, C, BF> A, B;
-            oload<R, C, BF>(A, ri, rd, h * U);
+            oload<R, C, BF>(A, ri, rd, 0, h);
             int it = 0;
             while (true) {
-                oload<R, C, BF>(B, ri, rd, (2 * (it + 1) + h) * U);
+                oload<R, C, BF>(B, ri, rd, it + 1, h);
                 __builtin_amdgcn_sched_barrier(0);
                 if (it + 1 >= iters) {
-                    ocompute<R, C, BF, true>(acc, A, xrow, Kb, m - (2 * it + h) * U);
+                    ocompute<R, C, BF, true>(acc, A, xrow, Kb, half_blocks<R, C, BF>(m, it, h));
                     break;
                 }
                 ocompute<R, C, BF, false>(acc, A, xrow, Kb, U);
                 __builtin_amdgcn_sched_barrier(0);
                 ++it;
-                oload<R, C, BF>(A, ri, rd, (2 * (it + 1) + h) * U);
+                oload<R, C, BF>(A, ri, rd, it + 1, h);
                 __builtin_amdgcn_sched_barrier(0);
                 if (it + 1 >= iters) {
-                    ocompute<R, C, BF, true>(acc, B, xrow, Kb, m - (2 * it + h) * U);
+                    ocompute<R, C, BF, true>(acc, B, xrow, Kb, half_blocks<R, C, BF>(m, it, h));
                     break;
                 }
                 ocompute<R, C, BF, false>(acc, B, xrow, Kb, U);
@@ -788,22 +799,22 @@ __global__ __launch_bounds__((kWaves<R, C, BF> * 64)) void spmm_vtile_chunk_kern
                 unsigned(m) * unsigned(S::RC * kEs));
             const int nq = (m + U - 1) / U, iters = (nq + 1) >> 1;
             OpsOf<R, C, BF> A, B;
-            oload<R, C, BF>(A, ri, rd, h * U);
+            oload<R, C, BF>(A, ri, rd, 0, h);
             int it = 0;
             while (true) {
-                oload<R, C, BF>(B, ri, rd, (2 * (it + 1) + h) * U);
+                oload<R, C, BF>(B, ri, rd, it + 1, h);
                 __builtin_amdgcn_sched_barrier(0);
                 if (it + 1 >= iters) {
-                    ocompute<R, C, BF, true>(acc[i], A, xrow, kbw, m - (2 * it + h) * U, jlo);
+                    ocompute<R, C, BF, true>(acc[i], A, xrow, kbw, half_blocks<R, C, BF>(m, it, h), jlo);
                     break;
                 }
                 ocompute<R, C, BF, false>(acc[i], A, xrow, kbw, U, jlo);
                 __builtin_amdgcn_sched_barrier(0);
                 ++it;
-                oload<R, C, BF>(A, ri, rd, (2 * (it + 1) + h) * U);
+                oload<R, C, BF>(A, ri, rd, it + 1, h);
                 __builtin_amdgcn_sched_barrier(0);
                 if (it + 1 >= iters) {
-                    ocompute<R, C, BF, true>(acc[i], B, xrow, kbw, m - (2 * it + h) * U, jlo);
+                    ocompute<R, C, BF, true>(acc[i], B, xrow, kbw, half_blocks<R, C, BF>(m, it, h), jlo);
                     break;
                 }
                 ocompute<R, C, BF, false>(acc[i], B, xrow, kbw, U, jlo);
