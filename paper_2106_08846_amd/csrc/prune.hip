@@ -593,21 +593,23 @@ size_t select_lds_bytes(int64_t nb) {
 //   4. prune_finish_kernel: one workgroup resolves the listed keys to tau and the last kept id
 //      among its equals, and turns the chunks' kept counts into their first positions;
 //   5. prune_place_kernel: every chunk writes its part of indptr, indices and data.
-// On that weight the five take 12, 25, 20, 15 and 18 us (the whole call 10.25 ms -> 88 us); with
+// On that weight the five take 12, 25, 15, 11 and 13 us (the whole call 10.25 ms -> 76 us); with
 // the list appended through one global counter and the last workgroup of step 3 doing step 4,
-// step 3 alone took 340 us (its atomics and release fences).  At 36864 blocks (768 x 768 in
-// 4 x 4) the call went from 131 to 44 us; below the one-workgroup limit (32768 blocks, 33 us)
-// the five launches would cost more than they save.
+// step 3 alone took 340 us (its atomics and release fences).  Chunks of 4096 ids (576 workgroups
+// where 256 run at once), 1024 ids per pass of step 5 and the k-th key's bin searched again in
+// step 4 cost 20, 18 and 15 us (88 us).  At 36864 blocks (768 x 768 in 4 x 4) the call went from
+// 131 to 34 us; below the one-workgroup limit (32768 blocks, 33 us) the five launches would cost
+// more than they save.
 // A k-th key outside the window (the sample misled), or a bin with more keys than a segment
 // holds, is resolved from all keys by the one workgroup of step 4 (a bin of equal keys needs
 // only one chunk's).  Ordering between the steps is the stream's: no workgroup waits for another.
 // The arrays between them live in the workspace's source-id array, which this path has no
 // other use for.
 constexpr int kSamples = 4 * kSelThreads;
-constexpr int kMaxChunks = 2048;
 constexpr int kMaxRanges = 1024;          // workgroups of the key kernel
 constexpr int kMaxHists = 256;            // workgroups of the histogram kernel
-constexpr int kMinChunkShift = 12;        // ids per chunk (log2), raised until kMaxChunks suffice
+constexpr int kMinChunkShift = 11;        // ids per chunk (log2), raised until
+constexpr int kWantChunks = 512;          // kWantChunks suffice: about one round of workgroups
 constexpr unsigned long long kInfKey = 0x7FF0000000000000ull;
 
 // The histogram's window: kBins bins of 2^shift bit patterns from lo on; hi is its last value.
@@ -616,8 +618,16 @@ struct Window {
     int shift;
 };
 
+// The range of key values that holds the k-th key, the keys in it and the wanted rank among
+// them: a bin of the window, or everything above or below the window.
+struct Target {
+    unsigned long long lo, hi;
+    long long count, rank;
+};
+
 struct SelectCtrl {
     Window win;
+    Target target;
     unsigned long long tau;
     int32_t last_eq;
 };
@@ -635,7 +645,7 @@ struct SelectArrays {
     unsigned long long *range;   // [2 * kMaxRanges]: smallest and largest finite key per workgroup
     unsigned *hist;              // [kBins]
     unsigned *above;             // [kMaxHists]: keys above the window, per workgroup
-    Chunk *chunk;                // [kMaxChunks]
+    Chunk *chunk;                // [kWantChunks] at most
     unsigned long long *list_key;
     int32_t *list_id;
     unsigned cap;                // list entries per chunk
@@ -653,7 +663,7 @@ SelectArrays select_arrays(void *src, int64_t nb) {
                                        ~uintptr_t(kSelectAlign - 1));
     SelectArrays a;
     a.chunk_shift = kMinChunkShift;
-    while (((nb - 1) >> a.chunk_shift) + 1 > kMaxChunks) ++a.chunk_shift;
+    while (((nb - 1) >> a.chunk_shift) + 1 > kWantChunks) ++a.chunk_shift;
     a.chunks = unsigned(((nb - 1) >> a.chunk_shift) + 1);
     a.ctrl = reinterpret_cast<SelectCtrl *>(p);
     a.range = reinterpret_cast<unsigned long long *>(p + 256);
@@ -785,7 +795,7 @@ __global__ __launch_bounds__(kSelThreads) void prune_hist_kernel(
     *reinterpret_cast<uint4 *>(&hist[4 * tid]) = make_uint4(0u, 0u, 0u, 0u);
     __syncthreads();
     const uint64_t stride = uint64_t(gridDim.x) * kSelThreads;
-    constexpr int kAhead = 4;
+    constexpr int kAhead = 8;
     unsigned above = 0;
     for (uint64_t b = uint64_t(blockIdx.x) * kSelThreads + tid; b < nb; b += stride * kAhead) {
         unsigned long long u[kAhead];
@@ -813,13 +823,6 @@ __global__ __launch_bounds__(kSelThreads) void prune_hist_kernel(
     for (int q = 0; q < 4; ++q)
         if (c[q]) atomicAdd(&A.hist[4 * tid + q], c[q]);
 }
-
-// The range of key values that holds the k-th key, the keys in it and the wanted rank among
-// them: a bin of the window, or everything above or below the window.
-struct Target {
-    unsigned long long lo, hi;
-    long long count, rank;
-};
 
 __device__ __forceinline__ Target find_target(unsigned nb, long long k, int hists,
                                               const SelectArrays &A, unsigned *wave_tot,
@@ -858,6 +861,7 @@ __device__ __forceinline__ Target find_target(unsigned nb, long long k, int hist
     return t;
 }
 
+// Two workgroups per CU: 64 registers.
 __global__ __launch_bounds__(kSelThreads) void prune_collect_kernel(
     const unsigned long long *__restrict__ keybits, unsigned nb, long long k, int hists,
     SelectArrays A) {
@@ -881,6 +885,7 @@ __global__ __launch_bounds__(kSelThreads) void prune_collect_kernel(
     load(b0);   // under the target's reductions
     if (tid == 0) s_n = 0;
     const Target t = find_target(nb, k, hists, A, wave_tot, &s_picked);   // ends with a barrier
+    if (blockIdx.x == 0 && tid == 0) A.ctrl->target = t;
 
     unsigned above = 0;
     unsigned long long kmin = ~0ull, kmax = 0ull;
@@ -917,8 +922,7 @@ __global__ __launch_bounds__(kSelThreads) void prune_collect_kernel(
 }
 
 __global__ __launch_bounds__(kSelThreads) void prune_finish_kernel(
-    const unsigned long long *__restrict__ keybits, unsigned nb, long long k, int hists,
-    SelectArrays A) {
+    const unsigned long long *__restrict__ keybits, unsigned nb, SelectArrays A) {
     constexpr int kList = 4096;   // candidates held in LDS; more are read from the segments
     __shared__ __align__(16) unsigned hist[kBins];
     __shared__ unsigned long long s_list[kList];
@@ -933,12 +937,12 @@ __global__ __launch_bounds__(kSelThreads) void prune_finish_kernel(
     __shared__ long long s_run;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int chunks = int(A.chunks);
-    static_assert(kMaxChunks == 2 * kSelThreads, "two chunks per thread");
+    static_assert(kWantChunks <= 2 * kSelThreads, "at most two chunks per thread");
     Chunk mine[2];
 #pragma unroll
     for (int q = 0; q < 2; ++q)
         mine[q] = 2 * tid + q < chunks ? A.chunk[2 * tid + q] : Chunk{0u, 0u, ~0ull, 0ull};
-    const Target t = find_target(nb, k, hists, A, wave_tot, &s_picked);
+    const Target t = A.ctrl->target;
 
     unsigned long long lo = mine[0].kmin < mine[1].kmin ? mine[0].kmin : mine[1].kmin;
     unsigned long long hi = mine[0].kmax > mine[1].kmax ? mine[0].kmax : mine[1].kmax;
@@ -1121,14 +1125,18 @@ __global__ __launch_bounds__(kSelThreads) void prune_finish_kernel(
     }
 }
 
-// One chunk of ids: the kept ones' columns, row starts and data, kSelThreads ids at a time.
+// One chunk of ids: the kept ones' columns, row starts and data, kPlaceIds ids at a time (four per
+// thread, so that two barriers place 4096 ids).
+constexpr int kPlacePer = 4;
+constexpr int kPlaceIds = kPlacePer * kSelThreads;
+
 __global__ __launch_bounds__(kSelThreads) void prune_place_kernel(
     const float *__restrict__ W, int64_t ldw, int32_t R, int32_t C, unsigned Kb, unsigned nb,
-    long long k, unsigned Nb, const unsigned long long *__restrict__ keybits, SelectArrays A, int32_t *__restrict__ indptr, int32_t *__restrict__ indices,
-    float *__restrict__ data) {
-    __shared__ unsigned wave_tot[kSelWaves];
-    __shared__ unsigned s_id[kSelThreads];
-    const int tid = threadIdx.x;
+    long long k, unsigned Nb, const unsigned long long *__restrict__ keybits, SelectArrays A,
+    int32_t *__restrict__ indptr, int32_t *__restrict__ indices, float *__restrict__ data) {
+    __shared__ unsigned s_cnt[kPlacePer * kSelWaves];   // kept ids per (part, wave), in id order
+    __shared__ unsigned s_id[kPlaceIds];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const unsigned long long tau = A.ctrl->tau;
     const int last_eq = A.ctrl->last_eq;
     const int64_t b0 = int64_t(blockIdx.x) << A.chunk_shift;
@@ -1138,26 +1146,51 @@ __global__ __launch_bounds__(kSelThreads) void prune_place_kernel(
     unsigned *Du = reinterpret_cast<unsigned *>(data);
     const unsigned RC = unsigned(R) * unsigned(C);
     int64_t pos0 = A.chunk[blockIdx.x].above;
-    unsigned long long u = b0 + tid < b1 ? keybits[b0 + tid] : 0ull;
-    for (int64_t base = b0; base < b1; base += kSelThreads) {
-        const int64_t b = base + tid;
-        const bool valid = b < b1;
-        const bool keep = valid && is_kept(u, int(b), tau, last_eq);
-        const int64_t bn = b + kSelThreads;
-        const unsigned long long un = bn < b1 ? keybits[bn] : 0ull;
-        unsigned ex, tot;
-        wg_scan(keep, ex, tot, wave_tot);
-        if (valid) {
-            const unsigned id = unsigned(b), i = id / Kb, j = id - i * Kb;
-            if (j == 0) indptr[i] = int32_t(pos0 + ex);
-            if (keep) {
-                indices[pos0 + ex] = int32_t(j);
-                if (RC == 1) Du[pos0 + ex] = Wu[int64_t(i) * ldw + j];
-                else s_id[ex] = id;
+    unsigned long long u[kPlacePer];
+    auto load = [&](int64_t base) {
+#pragma unroll
+        for (int q = 0; q < kPlacePer; ++q) {
+            const int64_t b = base + q * kSelThreads + tid;
+            u[q] = b < b1 ? keybits[b] : 0ull;
+        }
+    };
+    load(b0);
+    for (int64_t base = b0; base < b1; base += kPlaceIds) {
+        bool keep[kPlacePer];
+        unsigned below[kPlacePer];
+#pragma unroll
+        for (int q = 0; q < kPlacePer; ++q) {
+            const int64_t b = base + q * kSelThreads + tid;
+            keep[q] = b < b1 && is_kept(u[q], int(b), tau, last_eq);
+            const unsigned long long m = __ballot(keep[q]);
+            below[q] = unsigned(__popcll(m & ((1ull << lane) - 1ull)));
+            if (lane == 0) s_cnt[q * kSelWaves + wave] = unsigned(__popcll(m));
+        }
+        load(base + kPlaceIds);   // the next ids, under the placement
+        __syncthreads();
+        // Kept ids before each of this wave's parts, and in all: one entry per lane.
+        static_assert(kPlacePer * kSelWaves == 64, "one count per lane");
+        const unsigned mine = s_cnt[lane];
+        const unsigned incl = unsigned(wave_scan_incl(int(mine)));
+        const unsigned tot = unsigned(__builtin_amdgcn_readlane(int(incl), 63));
+#pragma unroll
+        for (int q = 0; q < kPlacePer; ++q) {
+            const int64_t b = base + q * kSelThreads + tid;
+            const unsigned ex =
+                unsigned(__builtin_amdgcn_readlane(int(incl - mine), q * kSelWaves + uniform(wave))) +
+                below[q];
+            if (b < b1) {
+                const unsigned id = unsigned(b), i = id / Kb, j = id - i * Kb;
+                if (j == 0) indptr[i] = int32_t(pos0 + ex);
+                if (keep[q]) {
+                    indices[pos0 + ex] = int32_t(j);
+                    if (RC == 1) Du[pos0 + ex] = Wu[int64_t(i) * ldw + j];
+                    else s_id[ex] = id;
+                }
             }
         }
+        __syncthreads();   // s_cnt is read; the kept ids are in s_id
         if (RC > 1) {
-            __syncthreads();
             const uint64_t total = uint64_t(tot) * RC;
             auto copy = [&](auto index) {   // 32-bit divisions where the element count allows
                 using I = decltype(index);
@@ -1170,10 +1203,9 @@ __global__ __launch_bounds__(kSelThreads) void prune_place_kernel(
             };
             if (total < (uint64_t(1) << 31)) copy(0u);
             else copy(uint64_t(0));
-            __syncthreads();
+            __syncthreads();   // s_id is free again
         }
         pos0 += tot;
-        u = un;
     }
     if (blockIdx.x == 0 && tid == 0) indptr[Nb] = static_cast<int32_t>(k);
 }
@@ -1285,8 +1317,7 @@ bsr_status launch_prune_wide(const float *W, int64_t ldw, int32_t R, int32_t C, 
     hipLaunchKernelGGL(prune_collect_kernel, dim3(A.chunks), dim3(kSelThreads), 0, st, keybits, n,
                        kk, hists, A);
     if ((s = launch_status()) != BSR_OK) return s;
-    hipLaunchKernelGGL(prune_finish_kernel, dim3(1), dim3(kSelThreads), 0, st, keybits, n, kk,
-                       hists, A);
+    hipLaunchKernelGGL(prune_finish_kernel, dim3(1), dim3(kSelThreads), 0, st, keybits, n, A);
     if ((s = launch_status()) != BSR_OK) return s;
     hipLaunchKernelGGL(prune_place_kernel, dim3(A.chunks), dim3(kSelThreads), 0, st, W, ldw, R, C,
                        unsigned(Kb), n, kk, unsigned(Nb), keybits, A, indptr, indices, data);
