@@ -43,9 +43,13 @@ constexpr int kDepthOf = PK == 2 ? 2 : 3;
 template <int PK>
 constexpr int kRingOf = kDepthOf<PK> + 1;
 // 64-column X chunks a persistent workgroup prefetches per row (fewer for split units, whose
-// operands need more registers).
-template <int PK>
-constexpr int kXChunksPersistent = PK == 2 ? 8 : 16;
+// operands need more registers).  A 64-token tile has four rows per wave and one bf16 column per
+// register: eight chunks were spilled to scratch memory, each load waited for before the next
+// one's, and two run faster although the rest of a row is loaded between the items (unplanned and
+// planned, 40%, 32768 tokens: 768 x 768 83 -> 57 and 73 -> 46 us, 768 x 512 72 -> 46 and 64 -> 40;
+// four 66 and 53, 55 and 45; two and then passes of eight with registers of their own 73 and 67).
+template <int PK, int TT>
+constexpr int kXChunksPersistent = TT == 64 ? 2 : (PK == 2 ? 8 : 16);
 
 // Empty owned rows, the stream and the combine of one (token tile, slice) item, shared by the
 // one-item and the persistent kernel.  `it` holds the wave's share and the LDS layout; the
@@ -715,7 +719,7 @@ __global__ __launch_bounds__(kNW * 64) void spmm_flat_persistent_kernel(const Ti
 
     constexpr int kXBytes = BF ? 2 : 4;
     constexpr int kRowsPerWave = TT / NW;
-    constexpr int kXC = kXChunksPersistent<PK> * 32 / TT;
+    constexpr int kXC = kXChunksPersistent<PK, TT>;
     static_assert(TT % NW == 0, "every wave stages the same number of rows");
 
     // X rows w + 16 r of a tile in registers, kXC 64-column chunks from column c0.  Rows past

@@ -68,3 +68,24 @@ def test_tile64_integer_inputs_exact(device):
     exact = O.spmm_loop(Xh, ip, ix, dt, N, bias).astype(np.float32)
     assert np.array_equal(bits(Y1), exact.view(np.uint32))
     assert np.array_equal(bits(Y0), bits(Y1))
+
+
+@pytest.mark.parametrize("K", [129, 191, 192, 256, 515])
+def test_tile64_persistent_column_remainders(device, K):
+    """More items than CUs at widths around the persistent kernel's passes over an X row (two
+    64-column chunks each): integer inputs, so both products are exact."""
+    g = rng(K)
+    N, T = 96, 20000
+    W = g.integers(1, 9, (N, K)).astype(np.float32)
+    Xh = g.integers(-8, 9, (T, K)).astype(np.float32)
+    bias = g.integers(-8, 9, N).astype(np.float32)
+    ip, ix, dt = O.prune(W, 32, 1, density=max(0.3, 128.5 / K))
+    assert len(ix) >= 128 * (N // 32), "the case must sit above the 64-token row threshold"
+    log(f"tile64 persistent K={K}")
+    M = upload(ip, ix, dt, N, K, bf16=True)
+    Y0, Y1, _ = run_pair(bf16_tensor(Xh), M, dev(bias), T, N)
+    rows = np.unique(np.concatenate([np.arange(64), np.arange(T - 33, T),
+                                     rng(7).choice(T, 200, replace=False)]))
+    exact = O.spmm_loop(Xh[rows], ip, ix, dt, N, bias).astype(np.float32)
+    assert np.array_equal(bits(Y1)[rows], exact.view(np.uint32))
+    assert np.array_equal(bits(Y0), bits(Y1))
