@@ -263,7 +263,7 @@ bsr_status bsr_spmm_batched_planned(const bsr_spmm_item_t *items, const bsr_plan
     for (size_t w = 0; w < work.size(); ++w) {
         const bsr_spmm_item_t &it = items[work[w]];
         const int R = it.W->R, C = it.W->C, dt = it.W->dtype;
-        // A trial plan with one slice decides whether the shape fits.
+        // A trial plan with one slice decides whether the shape fits (for every slice count).
         if ((kernel == BSR_KERNEL_AUTO || kernel == BSR_KERNEL_TILED) &&
             bsr::tiled_supported(R, C, dt) &&
             bsr::plan_tiled(it.X, it.T, it.ldx, it.W, it.ldy, 1, lds_limit).ok)
@@ -273,9 +273,8 @@ bsr_status bsr_spmm_batched_planned(const bsr_spmm_item_t *items, const bsr_plan
                  bsr::plan_kchunk(it.X, it.T, it.ldx, it.W, it.ldy, 1, lds_limit).base.ok)
             kind[w] = kKchunk;
         else if (const bsr::MtilePlan mp =
-                     kernel == BSR_KERNEL_AUTO
-                         ? bsr::plan_mtile(it.X, it.T, it.ldx, it.W, it.ldy, 1, lds_limit)
-                         : bsr::MtilePlan{};
+                     kernel == BSR_KERNEL_AUTO ? bsr::route_mtile(it, slices, cus, lds_limit)
+                                               : bsr::MtilePlan{};
                  mp.ok) {
             kind[w] = kMtile;
             tokens[w] = mp.tokens;
@@ -380,6 +379,7 @@ bsr_status bsr_spmm_batched_planned(const bsr_spmm_item_t *items, const bsr_plan
                 mtile[w] = bsr::MtileWork{
                     bsr::plan_mtile(it.X, it.T, it.ldx, it.W, it.ldy, S, lds_limit), it.X, it.T,
                     it.ldx, it.W, it.bias, it.Y, it.ldy};
+                if (!mtile[w].plan.ok) return BSR_ERR_UNSUPPORTED;   // nothing is launched yet
                 continue;
             }
             if (kind[w] == kKchunk || kind[w] == kVchunk) {

@@ -28,11 +28,14 @@
 #include <utility>
 
 #include "device_common.h"
+#include "mtile_plan.h"
 #include "spmm_tiled.h"
 
 namespace bsr {
 
 namespace {
+
+using namespace mtile;
 
 typedef float floatx2 __attribute__((ext_vector_type(2)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
@@ -40,40 +43,8 @@ typedef short shortx4 __attribute__((ext_vector_type(4)));
 typedef unsigned uintx2 __attribute__((ext_vector_type(2)));
 typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
 
-constexpr int kNW = 16;      // waves per workgroup
 constexpr int kDepth = 3;    // units in flight ahead of the one being multiplied
 constexpr int kRing = kDepth + 1;
-
-template <int R, int C, bool BF>
-struct MShape {
-    static constexpr bool kBf = BF && C % 4 == 0;   // bf16 matrix instructions, bf16 tile
-    static constexpr int TT = kBf ? 64 : 32;        // tokens per tile
-    static constexpr int H = 64 / TT;               // halves of a wave, on alternate blocks
-    static constexpr int F = R / 4;                 // groups of four rows
-    // A lane's weight load: LE instruction operands of one row, 16 bytes of it where a block's
-    // rows are that long (with 4-byte loads of 32-byte strided words the fp32 8x8 kernel waited
-    // on the texture addresser).  GP groups of 4 lanes (rows 4 f .. 4 f + 3) load a block.
-    static constexpr int LE = kBf ? C / 4 : (C >= 4 ? 4 : 1);
-    static constexpr int GP = (!kBf && C > 4 ? C / 4 : 1) * F;
-    static constexpr int GV = 16 / H;               // groups per half in one load
-    static constexpr int WL = C == 1 ? 2 : 1;       // weight loads per unit
-    static constexpr int NB = GV * WL / GP;         // blocks per half and unit
-    static constexpr int UB = H * NB;               // blocks per unit
-    static constexpr int RC = R * C;
-    static constexpr int kEs = BF ? 2 : 4;          // bytes per stored weight
-    static constexpr int kXs = kBf ? 2 : 4;         // bytes per X element in the tile
-    static constexpr int VW = C * kXs >= 16 ? 4 : C * kXs / 4;   // words per LDS read of X
-    static constexpr int PV = R * TT / 64;          // outputs per lane once the halves are summed
-    static_assert(NB <= 16 && NB * GP == GV * WL && (R == 4 || R == 8));
-};
-
-// Words (4 bytes) between token rows of a tile of `cols` columns: the columns and C zero ones,
-// rounded so that reads of VW words by consecutive tokens start VW banks apart (mod 2 VW).
-template <class S>
-int64_t tile_words(int64_t cols, int C) {
-    const int64_t w = ((cols + C) * S::kXs + 3) / 4;
-    return w + (((S::VW - w) % (2 * S::VW)) + 2 * S::VW) % (2 * S::VW);
-}
 
 struct MtileItem {
     const void *X;
@@ -130,10 +101,6 @@ __device__ __forceinline__ unsigned row_bcast(unsigned v) {
 // one by one (at 3072 outputs and 4096 tokens in bf16 4x4 blocks, 143 MB of write requests for 50
 // MB of Y), so a wave collects kGroup = 16 consecutive outputs per token in LDS and stores 64
 // bytes of a token with four adjacent lanes.  The buffer holds 32 tokens at a pitch of 20 words.
-constexpr int kGroup = 16;
-constexpr int kYPitch = 20;
-constexpr int kYWords = 32 * kYPitch;   // per wave
-
 // CH: several column chunks (else the tile holds whole rows of X); ST: staged Y stores.
 template <int R, int C, bool BF, bool CH, bool ST>
 __global__ __launch_bounds__(kNW * 64) void spmm_mtile_kernel(const MtileBatch batch) {
@@ -646,8 +613,8 @@ __global__ __launch_bounds__(kNW * 64) void spmm_mtile_kernel(const MtileBatch b
     }
 }
 
-// Least multiply-adds (stored weights x tokens) of a product for this kernel; smaller ones keep the
-// vector-ALU kernels, whose prologue is shorter (no unit tables, shares or combine).  Measured on
+// Least multiply-adds (stored weights x tokens) of a product for this kernel, by the plan that it
+// would have in a launch of its own; smaller ones keep the vector-ALU kernels, whose prologue is shorter (no unit tables, shares or combine).  Measured on
 // MI355X at a density of 0.1, vector-ALU / this kernel in us, 8x8 and 4x4 blocks:
 //   fp32  768x768, 777 tokens (46 M): 7.8 / 8.3, 7.4 / 8.4;  3072x768, 777 tokens (183 M):
 //         15.8 / 13.8, 17.2 / 15.8;  768x3072 (chunked, 183 M): 21.0 / 20.6, 19.8 / 20.9;
@@ -657,62 +624,6 @@ __global__ __launch_bounds__(kNW * 64) void spmm_mtile_kernel(const MtileBatch b
 constexpr int64_t kMinWork = int64_t(128) << 20;
 constexpr int64_t kMinWorkChunked = int64_t(192) << 20;
 constexpr int64_t kMinWorkBf16 = int64_t(16) << 20;
-
-template <int R, int C, bool BF>
-MtilePlan plan_shape(int64_t T, const bsr_matrix_t *W, int slices, size_t lds_limit) {
-    using S = MShape<R, C, BF>;
-    MtilePlan p{};
-    p.tokens = S::TT;
-    const int64_t K = W->n_cols, Nb = W->n_rows / R, Kb = K / C;
-    constexpr int64_t kPartials = int64_t(kNW) * S::PV * 64;   // words
-    auto a4 = [](int64_t w) { return (w + 3) & ~int64_t(3); };
-    // As few chunks as fit with the wanted slices; more slices (smaller tables and running sums)
-    // only when no chunk count fits.
-    constexpr int kMaxChunks = 16;
-    for (int64_t Sn = slices > 0 ? slices : 1;; Sn = Sn < Nb ? Sn * 2 : Nb + 1) {
-        if (Sn > Nb && Sn != (slices > 0 ? slices : 1)) return MtilePlan{};
-        const int64_t Su = Sn < Nb ? Sn : Nb;
-        const int64_t nr = (Nb + Su - 1) / Su;
-        for (int64_t nch = 1; nch <= kMaxChunks && nch <= Kb; ++nch) {
-            const int64_t kcb = (Kb + nch - 1) / nch;
-            if (kcb * (nch - 1) >= Kb) continue;   // the last chunk would be empty
-            const int64_t xp = tile_words<S>(kcb * C, C);
-            // Running sums take at most a third of LDS (more slices rather than narrower chunks).
-            if (nch > 1 && nr * 64 * S::PV * 4 > int64_t(lds_limit) / 3) break;
-            int64_t w = a4(S::TT * xp > kPartials ? S::TT * xp : kPartials);
-            const int64_t acc = w;
-            if (nch > 1) w += nr * 64 * S::PV;
-            const int64_t bias = w;
-            w += a4(nr * R);
-            const int64_t bound = w;
-            w += a4(nr * (nch + 1));
-            const int64_t up = w;
-            w = a4(w + nch * (nr + 1));
-            if (w * 4 > int64_t(lds_limit)) continue;
-            // Staging buffers where the rest leaves room (they do
-            // beside tiles of 768 columns, fp32 or bf16).
-            p.stage_words = 0;
-            if (nch == 1 && (w + kNW * kYWords) * 4 <= int64_t(lds_limit)) {
-                p.stage_words = int(w);
-                w += kNW * kYWords;
-            }
-            if (W->nnzb * R * C * T < (BF ? kMinWorkBf16 : nch > 1 ? kMinWorkChunked : kMinWork))
-                return MtilePlan{};
-            p.x_pitch = int(xp);
-            p.chunk_blocks = int(kcb);
-            p.nchunks = int(nch);
-            p.acc_words = int(acc);
-            p.bias_words = int(bias);
-            p.bound_words = int(bound);
-            p.up_words = int(up);
-            p.lds_bytes = size_t(w) * 4;
-            p.slices = int(Su);
-            p.num_tiles = int((T + S::TT - 1) / S::TT);
-            p.ok = true;
-            return p;
-        }
-    }
-}
 
 template <int R, int C, bool BF>
 bsr_status launch_shape(const MtileBatch &b, bool chunked, bool staged, dim3 grid, size_t lds,
@@ -750,6 +661,7 @@ void with_shape(int R, int C, bool bf, Fn &&f) {
 
 }  // namespace
 
+// The product's launch plan; ok depends on the layer and its arrays, never on the slices.
 MtilePlan plan_mtile(const void *X, int64_t T, int64_t ldx, const bsr_matrix_t *W, int64_t ldy,
                      int slices, size_t lds_limit) {
     const int R = W->R, C = W->C;
@@ -771,8 +683,22 @@ MtilePlan plan_mtile(const void *X, int64_t T, int64_t ldx, const bsr_matrix_t *
     return p;
 }
 
+MtilePlan route_mtile(const bsr_spmm_item_t &it, int slices, int cus, size_t lds_limit) {
+    const bool bf = it.W->dtype == BSR_BF16;
+    MtilePlan p = plan_mtile(it.X, it.T, it.ldx, it.W, it.ldy, 1, lds_limit);
+    if (!p.ok) return p;
+    const int64_t tiles = (it.T + p.tokens - 1) / p.tokens;
+    p = plan_mtile(it.X, it.T, it.ldx, it.W, it.ldy,
+                   slices > 0 ? slices : auto_slices(&tiles, 1, cus), lds_limit);
+    const int64_t macs = it.W->nnzb * it.W->R * it.W->C * it.T;
+    if (macs < (bf ? kMinWorkBf16 : p.nchunks > 1 ? kMinWorkChunked : kMinWork)) return MtilePlan{};
+    return p;
+}
+
 bsr_status launch_spmm_mtile(const MtileWork *work, int n, void *stream, const LaunchEvents &ev) {
     if (n < 1 || n > kMaxItems) return BSR_ERR_ARG;
+    for (int i = 0; i < n; ++i)
+        if (!work[i].plan.ok) return BSR_ERR_UNSUPPORTED;
     const int R = work[0].W->R, C = work[0].W->C, dtype = work[0].W->dtype;
     MtileBatch batch{};
     batch.n = n;

@@ -197,6 +197,9 @@ struct MtileWork {
 };
 MtilePlan plan_mtile(const void *X, int64_t T, int64_t ldx, const bsr_matrix_t *W, int64_t ldy,
                      int slices, size_t lds_limit);
+// Whether the automatic choice takes this kernel for a product (plan.ok); `slices`: as asked for by
+// the caller, 0 = automatic.
+MtilePlan route_mtile(const bsr_spmm_item_t &it, int slices, int cus, size_t lds_limit);
 bsr_status launch_spmm_mtile(const MtileWork *work, int n, void *stream, const LaunchEvents &ev);
 
 // The vector-ALU tile kernel (shapes without a matrix-core kernel: 1 x C, 2x1 .. 8x1, 2x2 ..

@@ -105,3 +105,40 @@ def test_mtile_infinities_and_pitch(device, R, C, bf16):
     X[:, :C] = 0.0
     check_spmm(X, M, None, Yb[:, 3:3 + N], bf16=bf16)
     assert bool((Yb[:, :3] == 7.0).all()) and bool((Yb[:, 3 + N:] == 7.0).all())
+
+
+def check_batch(products, dense, kernel=None, slices=None, seed=0):
+    """A batched call's outputs (Y filled with NaN before) against the oracle on sampled tokens."""
+    for _, _, _, Y in products:
+        Y.fill_(float("nan"))
+    B.bsr_spmm_batched(products, kernel=kernel, slices=slices)
+    g = np.random.Generator(np.random.PCG64(seed))
+    for (Xd, M, bias, Y), X in zip(products, dense):
+        assert bool(torch.isfinite(Y).all()), "outputs were not written"
+        rows = np.unique(np.r_[0, X.shape[0] - 1, g.integers(0, X.shape[0], 40)])
+        check_spmm(X, M, host(bias), Y, rows=rows, bf16=M.data.dtype == torch.bfloat16)
+
+
+# Layers whose plan needs other slices than the launch's automatic (None) or asked-for count, as the
+# launch's search and the one-slice search visit different counts.
+SLICES = [(8, 8, 1024, 1256, 2560, 0.05, None, False), (4, 4, 1120, 1256, 2560, 0.05, None, False),
+          (8, 1, 896, 1268, 2560, 0.05, None, False), (8, 8, 1024, 1256, 2560, 0.3, None, False),
+          (8, 8, 256, 19720, 700, 0.05, None, True), (8, 8, 32, 20000, 700, 0.5, 3, False),
+          (8, 1, 32, 20160, 700, 0.5, 3, False), (8, 8, 32, 20000, 700, 0.5, 5, False)]
+
+
+@pytest.mark.parametrize("case", range(len(SLICES)))
+def test_mtile_slices_of_the_launch(device, case):
+    """Alone and beside another product of the launch, whatever the slice count."""
+    R, C, N, K, T, d, slices, bf16 = SLICES[case]
+    log(f"mtile launch slices {R}x{C} {'bf16' if bf16 else 'f32'} {N}x{K} T={T} d={d} S={slices}")
+    products, dense = [], []
+    for i, (n, k) in enumerate([(N, K), (768, 768)]):
+        M = matrix(n, k, R, C, d, 30 + i, False)
+        X, Xd = inputs(T, k, 30 + i, bf16)
+        products.append((Xd, M.to_bf16() if bf16 else M, dev(np.linspace(-1, 1, n).astype(np.float32)),
+                         torch.empty((T, n), device="cuda:0")))
+        dense.append(X)
+    check_batch(products[:1], dense, slices=slices)
+    check_batch(products, dense, slices=slices)
+    check_batch(products[::-1], dense[::-1], slices=slices)

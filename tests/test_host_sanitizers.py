@@ -4,9 +4,11 @@
   (tests/host/validate_fuzz.cpp) through hostile sizes, pitches, counts, enum values and
   pointers, honouring each check's documented preconditions;
 * oracle/cpu_oracle.c, the C oracle, on random BSR matrices with every array allocated to its
-  exact size (tests/host/oracle_fuzz.c), checked against a plain loop.
+  exact size (tests/host/oracle_fuzz.c), checked against a plain loop;
+* csrc/mtile_plan.h, the small-block matrix kernel's planner, over layer sizes and slice counts
+  (tests/host/mtile_plan_scan.cpp).
 
-Both are built with g++/gcc (host code only, no GPU code) and must run clean: any sanitizer
+They are built with g++/gcc (host code only, no GPU code) and must run clean: any sanitizer
 report aborts the program with a non-zero status.
 """
 import os
@@ -47,3 +49,13 @@ def test_c_oracle_under_sanitizers(tmp_path):
     _build_and_run(["gcc", "-std=c11", *SAN,
                     os.path.join(ROOT, "tests", "host", "oracle_fuzz.c"),
                     os.path.join(ROOT, "oracle", "cpu_oracle.c"), "-o", exe, "-lm"], exe)
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+def test_small_block_planner_scan(tmp_path):
+    """A layer that fits the small-block kernel with one slice fits with every slice count (the
+    kernel is chosen before the launch's slices are known), and the search ends for each."""
+    exe = str(tmp_path / "mtile_plan_scan")
+    _build_and_run(["g++", "-std=c++17", *SAN,
+                    "-I", os.path.join(ROOT, "paper_2106_08846_amd", "csrc"),
+                    os.path.join(ROOT, "tests", "host", "mtile_plan_scan.cpp"), "-o", exe], exe)
