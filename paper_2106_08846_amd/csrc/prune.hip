@@ -22,6 +22,7 @@
 #include <mutex>
 
 #include "device_common.h"
+#include "prune_key.h"
 
 namespace bsr {
 
@@ -39,44 +40,8 @@ std::mutex g_scratch_mutex;
 constexpr int kKeyThreads = 256;
 constexpr int kSelThreads = 1024;
 constexpr int kSelWaves = kSelThreads / 64;
-constexpr unsigned long long kNaNKey = 0x7FF8000000000000ull;
 
-// Blocks' keys, one thread per block.  The elements of a block are visited in the sequential
-// order of the definition, sixteen loads issued before the sixteen dependent fp64 operations that use
-// them: with one load per operation a 32 x 32 block waited 1024 times for memory.
-template <bool kL1>
-__device__ __forceinline__ unsigned long long block_key(const float *__restrict__ base,
-                                                        int64_t ldw, int32_t R, int32_t C) {
-    constexpr int kAhead = 16;
-    const unsigned n = unsigned(R) * unsigned(C);
-    double s = 0.0;
-    const float *row = base;
-    int c = 0;
-    auto next = [&]() -> float {
-        const float x = row[c];
-        if (++c == C) {
-            c = 0;
-            row += ldw;
-        }
-        return x;
-    };
-    auto add = [&](float v) {
-        const double x = static_cast<double>(v);
-        if constexpr (kL1) s = __dadd_rn(s, fabs(x));
-        else s = __fma_rn(x, x, s);
-    };
-    unsigned e = 0;
-    for (; e + kAhead <= n; e += kAhead) {
-        float v[kAhead];
-#pragma unroll
-        for (int q = 0; q < kAhead; ++q) v[q] = next();
-#pragma unroll
-        for (int q = 0; q < kAhead; ++q) add(v[q]);
-    }
-    for (; e < n; ++e) add(next());
-    return s != s ? kNaNKey : static_cast<unsigned long long>(__double_as_longlong(s));
-}
-
+// Blocks' keys, one thread per block.
 template <bool kL1>
 __global__ __launch_bounds__(kKeyThreads) void prune_keys_kernel(
     const float *__restrict__ W, int64_t ldw, int32_t R, int32_t C, int64_t Kb, int64_t nb,
