@@ -362,7 +362,7 @@ constexpr int kPieces = 3;
 constexpr int kPlane = kKB * kD;   // elements of a plane: 64 rows of 64 bf16, 8-element chunks
                                    // of a row swizzled by its row so that equal chunks of eight
                                    // consecutive rows lie in different banks
-constexpr float kWeightScale = 0x1p64f;
+constexpr float kWeightExp = 64.0f;
 
 __device__ __forceinline__ unsigned cvt_pair(float a, float b) {   // round to nearest even
     const floatx2 v = {a, b};
@@ -421,16 +421,18 @@ __device__ __forceinline__ floatx16 mfma_split(const uintx4 (&a)[kPieces],
     return mfma_bf16(a[0], b[0], c);
 }
 
-// scale * exp(x) for x <= 0 (scale a power of two): 2^t of the rounded product t = x log2(e), times
-// 1 + r ln 2 for what the rounding and log2(e)'s low bits left out (r < 2^-17 where exp(x) is not
-// negligible).  About half of expf's instructions: x is never positive, so nothing overflows.
-__device__ __forceinline__ float exp_scaled(float x, float scale) {
+// 2^64 exp(x) for x <= 0: 2^u of u = x log2(e) + 64, rounded to z + 64 with z = u - 64 exact, times
+// 1 + r ln 2 for what the roundings and log2(e)'s low bits left out (r < 2^-16 where exp(x) is not
+// negligible).  About half of expf's instructions: x is never positive, so nothing overflows; and the
+// 2^64 inside the hardware's 2^u, which is never a subnormal number, keep weights below 2^-126.
+__device__ __forceinline__ float exp_scaled(float x) {
+#pragma clang fp contract(off)
     constexpr float kLog2e = 0x1.715476p+0f, kLog2eLo = 0x1.4ae0bfp-26f, kLn2 = 0x1.62e430p-1f;
     x = fmaxf(x, -200.0f);   // -inf has no remainder; the weight is 0 either way
-    const float t = x * kLog2e;
-    float r = __builtin_fmaf(x, kLog2e, -t);
+    const float t = x * kLog2e, u = t + kWeightExp, z = u - kWeightExp;
+    float r = __builtin_fmaf(x, kLog2e, -z);
     r = __builtin_fmaf(x, kLog2eLo, r);
-    return __builtin_amdgcn_exp2f(t) * __builtin_fmaf(r, kLn2 * scale, scale);
+    return __builtin_amdgcn_exp2f(u) * __builtin_fmaf(r, kLn2, 1.0f);
 }
 
 // A tile's running state, by lane: query l % 32, outputs as documented at the stores.
@@ -468,7 +470,7 @@ __device__ __forceinline__ float online_softmax(TileState &st, floatx16 &s) {
     float ps = 0.0f;
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
-        s[v] = kSplit ? exp_scaled(s[v] - mn, kWeightScale) : expf(s[v] - mn);
+        s[v] = kSplit ? exp_scaled(s[v] - mn) : expf(s[v] - mn);
         ps += s[v];
     }
     ps += __shfl_xor(ps, 32);

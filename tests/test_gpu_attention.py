@@ -94,6 +94,38 @@ def test_attention_out_of_range_operands(device, batch, seq, heads, kind):
     check_attention(Q, K, V, torch.from_numpy(got), batch, seq, heads)
 
 
+SHARED_KEYS = [(2, 300, 3), (16, 384, 8), (16, 512, 6), (48, 128, 12)]
+SHARED_IDS = ["key_halves", "twelve_tiles", "eight_tiles", "four_tiles"]
+
+
+@pytest.mark.parametrize("batch,seq,heads", SHARED_KEYS, ids=SHARED_IDS)
+@pytest.mark.parametrize("kind", ["weights", "values", "keys"])
+def test_attention_smallest_operands(device, batch, seq, heads, kind):
+    """Subnormal softmax weights, values and keys keep their share of the result: the fp32 bound,
+    which is relative to it, is met where nothing larger is there to hide them.  (Weights of 2^-130
+    are off by up to 2^-150: 2^-20, below the bound's 66 * 2^-24 * 90 for scores of -90.)"""
+    g = rng(9800 + batch + seq)
+    T, W = batch * seq, heads * 64
+    Q, K, V = [g.standard_normal((T, W)).astype(np.float32) for _ in range(3)]
+    one = np.s_[seq:2 * seq, 64:128]   # sequence 1, head 1
+    if kind == "weights":    # the first key outweighs all others and has values of zero
+        Q[one] = 0.0
+        K[one] = 0.0
+        Q[seq:2 * seq, 64] = 8.0
+        K[seq + 1:2 * seq, 64] = g.uniform(-90.5, -88.0, seq - 1).astype(np.float32)
+        V[seq, 64:128] = 0.0
+        V[one] *= np.float32(2.0 ** 20)
+    elif kind == "values":
+        V[one] *= np.float32(2.0 ** -130)
+    else:
+        K[one] *= np.float32(2.0 ** -130)
+    log(f"attention smallest {kind} {batch}x{seq}x{heads}")
+    ctx = B.bsr_attention(dev(Q), dev(K), dev(V), batch, seq, heads)
+    check_attention(Q, K, V, ctx, batch, seq, heads)
+    if kind != "keys":
+        assert bool((ctx[seq:2 * seq, 64:128] != 0).all())
+
+
 def test_attention_on_a_fused_qkv_output(device):
     """Q, K, V as column views of one [T, 3*768] buffer (row pitch 2304), output pitched too."""
     g = rng(9600)
