@@ -384,7 +384,7 @@ LIBBSR_API bsr_status bsr_spmm_batched_planned(const bsr_spmm_item_t *items,
  * Rows are tokens (batch-major), head h owns columns h*64 .. h*64 + 63; no mask.  fp32 inputs and
  * output, fp32 accumulation, online softmax.  Long or many sequences form each fp32 product from
  * bf16 pieces of both operands (six exact cross terms; what is left out is below half an ulp of the
- * product); operands outside [2^-60, 2^40) in magnitude, other than zero, use fp32 products.
+ * product); where operands of 2^48 or more, infinities or NaN occur, fp32 products take over.
  * Q, K, V: device fp32 with row pitches ldq, ldk, ldv >= heads * 64, 16-byte aligned bases and
  *   pitches that are multiples of 4.  O: device fp32, row pitch ldo >= heads * 64; it must not
  *   overlap Q, K or V.  head_dim must be 64.  batch = 0 or seq = 0 is a no-op.

@@ -4,7 +4,8 @@
 //   ctx[b, s, head h] = sum_j softmax_j(scale * <Q[b,s,h], K[b,j,h]>) V[b,j,h]
 //
 // Tokens are rows t = b * seq + s of Q, K, V and ctx; head h owns columns h*64 .. h*64 + 63.
-// No mask: every token attends to every token of its sequence.  fp32 throughout.
+// No mask: every token attends to every token of its sequence.  fp32 inputs, sums and outputs; the
+// products are fp32, or exact cross terms of bf16 pieces in the matrix-core version below.
 //
 // Short sequences with few queries run on the vector ALUs: one workgroup of 64 threads computes
 // 8 queries of one (sequence, head).  The keys are
@@ -343,15 +344,19 @@ __global__ __launch_bounds__(64 * kKS) void attention_split_kernel(
 // instructions with every fp32 operand x as three bf16 pieces, x = x0 + x1 + x2 exactly, each the
 // remainder rounded to nearest (|x1| <= 2^-9 |x|, |x2| <= 2^-18 |x|).  Of the nine cross terms the
 // six with i + j <= 2 are formed, each exact in fp32; the three left out are below 2^-25 |x y|
-// together, half an ulp of the fp32 product that they belong to.  The weights are carried as 2^64 exp(s - m),
-// and so is their sum, so that no piece of a weight underflows before the weight would.
+// together, half an ulp of the fp32 product that they belong to.  The weights are carried as
+// 2^24 exp(s - m), as is their sum, and the values as 2^24 V: the last bit of any fp32 number, 2^-149,
+// is then a normal bf16 number, so the pieces of a weight or a value are exact down to the smallest
+// one.  (Pieces of a query or a key below 2^-102 may lose their last bits: less than 2^-126 of an
+// operand, times one below 2^48, changes a score by less than 2^-70.)
 // Every group's output is summed from zero and then added to the running output, so the long sum
 // is rounded once per 32 keys.  Against fp64, 384 tokens x 16 heads, normal inputs: 2-norm error
 // 2.4e-7, where fp32 matrix instructions with one running sum gave 4.5e-7.
 // 16 x 384 tokens, 16 heads: 104 -> 70 us; 8 x 512, 12 heads: 88 -> 61 us (MI355X); what bounds it
 // now is vector instructions (softmax and splitting) and matrix instructions in turn.
-// The pieces are exact only for operands that are zero or in [2^-60, 2^40); a workgroup that stages
-// any other element (infinities and NaN among them) starts over on fp32 matrix instructions.
+// Operands have to lie below 2^48, so that no score and no sum over 2^31 keys overflows.  A workgroup
+// that stages any other element (infinities and NaN among them) goes on from that block of keys on
+// fp32 matrix instructions.
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef float floatx2 __attribute__((ext_vector_type(2)));
 typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
@@ -362,7 +367,7 @@ constexpr int kPieces = 3;
 constexpr int kPlane = kKB * kD;   // elements of a plane: 64 rows of 64 bf16, 8-element chunks
                                    // of a row swizzled by its row so that equal chunks of eight
                                    // consecutive rows lie in different banks
-constexpr float kWeightExp = 64.0f;
+constexpr float kWeightExp = 24.0f, kWeightScale = 0x1p24f, kValueScale = 0x1p24f;
 
 __device__ __forceinline__ unsigned cvt_pair(float a, float b) {   // round to nearest even
     const floatx2 v = {a, b};
@@ -389,17 +394,13 @@ __device__ __forceinline__ void split8(const float (&v)[8], uintx4 (&out)[kPiece
     }
 }
 
-// Range of the magnitudes seen, as bit patterns (zero counts as neither large nor small).
+// The largest magnitude seen, as a bit pattern (infinities and NaN above all numbers).
 struct Range {
-    unsigned lo = ~0u, hi = 0u;
+    unsigned hi = 0u;
     __device__ __forceinline__ void add(float x) {
-        const unsigned b = __float_as_uint(x) & 0x7fffffffu;
-        lo = min(lo, b - 1u);   // zero wraps to the largest value
-        hi = max(hi, b);
+        hi = max(hi, __float_as_uint(x) & 0x7fffffffu);
     }
-    __device__ __forceinline__ bool outside() const {
-        return lo < 0x21800000u - 1u || hi >= 0x53800000u;   // 2^-60, 2^40
-    }
+    __device__ __forceinline__ bool outside() const { return hi >= 0x57800000u; }   // 2^48
 };
 
 // Byte offset of chunk c of row r in a plane.
@@ -421,10 +422,10 @@ __device__ __forceinline__ floatx16 mfma_split(const uintx4 (&a)[kPieces],
     return mfma_bf16(a[0], b[0], c);
 }
 
-// 2^64 exp(x) for x <= 0: 2^u of u = x log2(e) + 64, rounded to z + 64 with z = u - 64 exact, times
+// 2^24 exp(x) for x <= 0: 2^u of u = x log2(e) + 24, rounded to z + 24 with z = u - 24 exact, times
 // 1 + r ln 2 for what the roundings and log2(e)'s low bits left out (r < 2^-16 where exp(x) is not
 // negligible).  About half of expf's instructions: x is never positive, so nothing overflows; and the
-// 2^64 inside the hardware's 2^u, which is never a subnormal number, keep weights below 2^-126.
+// 2^24 inside the hardware's 2^u, which is never a subnormal number, keep the smallest weights.
 __device__ __forceinline__ float exp_scaled(float x) {
 #pragma clang fp contract(off)
     constexpr float kLog2e = 0x1.715476p+0f, kLog2eLo = 0x1.4ae0bfp-26f, kLn2 = 0x1.62e430p-1f;
@@ -457,7 +458,7 @@ __device__ __forceinline__ void mask_keys(floatx16 &s, int kg, int hh, int seq) 
     }
 }
 
-// Running maximum, weights (in s; kSplit: times 2^64) and running sum; the factor by which the
+// Running maximum, weights (in s; kSplit: times 2^24) and running sum; the factor by which the
 // outputs so far are to be rescaled is returned.
 template <bool kSplit>
 __device__ __forceinline__ float online_softmax(TileState &st, floatx16 &s) {
@@ -479,12 +480,13 @@ __device__ __forceinline__ float online_softmax(TileState &st, floatx16 &s) {
     return corr;
 }
 
-// All of a tile's keys on bf16 pieces; false (in every thread of the workgroup) when an operand
-// is out of the pieces' range.
+// A tile's keys on bf16 pieces.  At the first block with an operand out of the pieces' range (a query
+// counts with the first) it stops and returns false, the block's first key in `left`, in every thread
+// of the workgroup.  The state carries the scales of the weights and the values.
 template <int kWQ, int kKS>
 __device__ __forceinline__ bool tile_split(TileState &st, const float *qp, const float *Kh,
                                            int64_t ldk, const float *Vh, int64_t ldv, int seq,
-                                           float scale, char *smem, int *s_bad) {
+                                           float scale, char *smem, int *s_bad, int &left) {
     constexpr int kThreads = kWQ * kKS * 64;
     char *Kp = smem, *Vp = smem + kPieces * kPlane * 2;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, ks = wave / kWQ;
@@ -539,7 +541,10 @@ __device__ __forceinline__ bool tile_split(TileState &st, const float *qp, const
                 v[e] = key < seq ? x : 0.0f;
             }
 #pragma unroll
-            for (int e = 0; e < 8; ++e) range.add(v[e]);
+            for (int e = 0; e < 8; ++e) {
+                range.add(v[e]);
+                v[e] *= kValueScale;
+            }
             uintx4 u[kPieces];
             split8(v, u);
 #pragma unroll
@@ -548,7 +553,10 @@ __device__ __forceinline__ bool tile_split(TileState &st, const float *qp, const
         }
         if (range.outside()) *s_bad = 1;
         __syncthreads();
-        if (*s_bad) return false;   // the same word in every thread
+        if (*s_bad) {   // the same word in every thread
+            left = k0;
+            return false;
+        }
 
 #pragma unroll
         for (int gi = 0; gi < kKB / 32 / kKS; ++gi) {
@@ -606,14 +614,14 @@ __device__ __forceinline__ bool tile_split(TileState &st, const float *qp, const
     return true;
 }
 
-// All of a tile's keys on v_mfma_f32_32x32x2_f32, for operands of any value.  Scores: step s
+// A tile's keys from k0 on, on v_mfma_f32_32x32x2_f32, for operands of any value.  Scores: step s
 // (s < 32) contracts dimension s + 32hh in slot hh: A = K[key l%32][s + 32hh] (LDS), B = the lane's
 // pre-scaled q[s + 32hh].  Output: step v contracts the two keys that register v holds in the two
 // halves: A = V[that key][32t + l%32] (LDS; output column tile t = 0, 1), B = the lane's weight p[v].
 template <int kWQ, int kKS>
 __device__ __forceinline__ void tile_fp32(TileState &st, const float *qp, const float *Kh,
                                           int64_t ldk, const float *Vh, int64_t ldv, int seq,
-                                          float scale, char *smem) {
+                                          float scale, char *smem, int k0) {
     constexpr int kThreads = kWQ * kKS * 64;
     float *Ks = reinterpret_cast<float *>(smem), *Vs = Ks + kKB * kPitch;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, ks = wave / kWQ;
@@ -625,7 +633,7 @@ __device__ __forceinline__ void tile_fp32(TileState &st, const float *qp, const 
 #pragma unroll
         for (int e = 0; e < 4; ++e) q[d + e] = v[e] * scale;
     }
-    for (int k0 = 0; k0 < seq; k0 += kKB) {
+    for (; k0 < seq; k0 += kKB) {
         __syncthreads();   // the previous block's LDS reads are done
         for (int i = tid; i < kKB * (kD / 4); i += kThreads) {
             const int r = i >> 4, c4 = (i & 15) * 4, key = k0 + r;
@@ -693,9 +701,19 @@ void attention_mfma_kernel(
     const float *Kh = K + tok0 * ldk + h * kD, *Vh = V + tok0 * ldv + h * kD;
     TileState st;
     tile_reset(st);
-    if (!tile_split<kWQ, kKS>(st, qp, Kh, ldk, Vh, ldv, seq, scale, smem, &s_bad)) {
-        tile_reset(st);
-        tile_fp32<kWQ, kKS>(st, qp, Kh, ldk, Vh, ldv, seq, scale, smem);
+    int left = 0;
+    if (!tile_split<kWQ, kKS>(st, qp, Kh, ldk, Vh, ldv, seq, scale, smem, &s_bad, left)) {
+        st.l *= 1.0f / kWeightScale;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            st.o0[v] *= 1.0f / (kWeightScale * kValueScale);
+            st.o1[v] *= 1.0f / (kWeightScale * kValueScale);
+        }
+        tile_fp32<kWQ, kKS>(st, qp, Kh, ldk, Vh, ldv, seq, scale, smem, left);
+    } else {
+        // Outputs are quotients, so a common scale does not show.  (With this line before the return
+        // above, the compiler spilled 26 registers.)
+        st.l *= kValueScale;
     }
     float &m = st.m, &l = st.l;
     floatx16 &o0 = st.o0, &o1 = st.o1;

@@ -126,6 +126,22 @@ def test_attention_smallest_operands(device, batch, seq, heads, kind):
         assert bool((ctx[seq:2 * seq, 64:128] != 0).all())
 
 
+@pytest.mark.parametrize("batch,seq,heads", SHARED_KEYS, ids=SHARED_IDS)
+@pytest.mark.parametrize("block", [0, 1, -1], ids=["first", "second", "last"])
+def test_attention_goes_on_in_fp32(device, batch, seq, heads, block):
+    """A key too large for the bf16 pieces in the first, second or last block of 64 keys (its
+    dimension is zero in every query): the blocks before it keep their part of the result."""
+    g = rng(9900 + batch + seq)
+    T, W = batch * seq, heads * 64
+    Q, K, V = [g.standard_normal((T, W)).astype(np.float32) for _ in range(3)]
+    key = seq - 1 if block < 0 else 64 * block + 17
+    Q[seq:2 * seq, 64 + 9] = 0.0
+    K[seq + key, 64 + 9] = np.float32(2.0 ** 50)
+    log(f"attention on in fp32 from key {key} {batch}x{seq}x{heads}")
+    ctx = B.bsr_attention(dev(Q), dev(K), dev(V), batch, seq, heads)
+    check_attention(Q, K, V, ctx, batch, seq, heads)
+
+
 def test_attention_on_a_fused_qkv_output(device):
     """Q, K, V as column views of one [T, 3*768] buffer (row pitch 2304), output pitched too."""
     g = rng(9600)
