@@ -12,7 +12,8 @@
 //     [32][K] is staged once into LDS as fp32 (bf16 widened, exactly) with a row pitch XP that
 //     makes a read of one column segment by the 32 tokens hit distinct banks;
 //   * each wave walks whole block-rows of the slice, round robin; lane l is token l % 32 of
-//     half l / 32, and the two halves take alternate chunks of U blocks of the row;
+//     half l / 32, and the two halves take alternate blocks of the row (1x1 and bf16: alternate
+//     chunks of U blocks);
 //   * a lane accumulates the R outputs of its token over its chunks in fp32 (block column c
 //     outer, output row r inner); the halves are summed at the row end (both halves then hold
 //     the same bits) and each half stores its share of Y[t][iR .. iR + R);
@@ -174,6 +175,12 @@ struct DShape {
     // 4x4 and 8x1 ran 7-20% faster with the larger chunks).
     static constexpr int U = RC == 1 ? 8 : (64 / RC >= 16 ? 16 : (64 / RC < 1 ? 1 : 64 / RC));
     static constexpr int NWORDS = U * RC;
+    // The halves of a wave take alternate blocks of a row, or (1x1) alternate chunks of U blocks.
+    // Alternate blocks split a row evenly: a row of two 1x32 blocks ran on one half otherwise, and
+    // 1x4 at 3072 columns, density 0.05, 1881 tokens took 351 us against 236.  Long rows of 1x1
+    // blocks gain little, and every other word of a load is loaded for nothing: 264 x 1024, density
+    // 0.3, 725 tokens 12.5 us against 10.9 with chunks, 1260 x 3072, 0.05, 1881 tokens 130 and 126.
+    static constexpr bool kAlternate = RC > 1;
     static constexpr int NWV = (NWORDS + 15) / 16;   // weight registers
     static constexpr int VW = VShape<R, C>::VW;
     static_assert(U <= 16 && NWORDS <= 64, "a chunk's columns fit one 16-lane row");
@@ -185,16 +192,16 @@ constexpr int kUnits = BF ? VShape<R, C>::U : DShape<R, C>::U;
 
 template <int R, int C>
 struct DOps {
-    int j;                        // column of block (lane % 16) of the half's chunk
-    float w[DShape<R, C>::NWV];   // word 16 k + lane % 16 of the half's chunk
+    int j;                        // column of slot lane % 16 of the half's blocks
+    float w[DShape<R, C>::NWV];   // word 16 k + lane % 16 of the half's blocks
 };
 
 // Iteration `it` of a row: blocks 2 U it .. 2 U (it + 1) - 1, half h holding the blocks of its
-// parity (slot u: block 2 u + h), so that a short row is split evenly between the halves (with U
-// consecutive blocks per half a row of two 1x32 blocks ran on one half).  Ranges as in vload: past
-// the row's end a load returns 0 and touches no memory.  Lane l reads word 16 k + l % 16 of its
-// half's weights and the column of slot l % 16; lanes past the chunk read words that no broadcast
-// selects.
+// parity (slot u: block 2 u + h), or U consecutive ones (kAlternate).  Ranges as in vload: past the
+// row's end a load returns 0 and touches no memory.  Lane l reads word 16 k + l % 16 of its half's
+// weights and the column of slot l % 16; lanes past the chunk read words that no broadcast selects.
+// The whole offset is in the vector offset: with the iteration's part in the scalar offset (range-
+// checked as well) the kernels took 2 to 30% longer (8x1, 1024 x 2304, 35 tokens: 19.1 and 25.2 us).
 template <int R, int C>
 __device__ __forceinline__ void dload(DOps<R, C> &ops, __amdgpu_buffer_rsrc_t ri,
                                       __amdgpu_buffer_rsrc_t rd, int it) {
@@ -202,15 +209,14 @@ __device__ __forceinline__ void dload(DOps<R, C> &ops, __amdgpu_buffer_rsrc_t ri
     constexpr int RC = S::RC;
     static_assert(RC >= 16 ? RC % 16 == 0 : 16 % RC == 0, "lane i's slot is i / RC past register k's");
     const int i = threadIdx.x & 15, h = (threadIdx.x & 63) >> 5, base = 2 * it * S::U;
-    ops.j = int(__builtin_amdgcn_raw_buffer_load_b32(ri, (base + 2 * i + h) * 4, 0, 0));
-    // Word 16 k + i of slot u = (16 k + i) / RC lies (u + h) RC words further on; the whole offset
-    // is in the range-checked vector offset (a scalar offset past the range would escape the
-    // check).
-    const int v0 = (base * RC + (h + i / RC) * RC + i) * 4;
+    ops.j = int(__builtin_amdgcn_raw_buffer_load_b32(
+        ri, (base + (S::kAlternate ? 2 * i + h : S::U * h + i)) * 4, 0, 0));
+    // Alternate blocks: word 16 k + i of slot u = (16 k + i) / RC lies (u + h) RC words further on.
+    const int v0 = (base * RC + (S::kAlternate ? h + i / RC : S::U * h) * RC + i) * 4;
 #pragma unroll
     for (int k = 0; k < S::NWV; ++k)
         ops.w[k] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(
-            rd, v0 + (16 * k / RC * RC + 16 * k) * 4, 0, 0));
+            rd, v0 + ((S::kAlternate ? 16 * k / RC * RC : 0) + 16 * k) * 4, 0, 0));
 }
 
 // acc += w * x with w the value of lane L (0 .. 15, a constant once the caller's loops are
@@ -359,7 +365,7 @@ __device__ __forceinline__ void oload(OpsOf<R, C, BF> &ops, __amdgpu_buffer_rsrc
 // Blocks of half h in iteration `it` of a row of m blocks.
 template <int R, int C, bool BF>
 __device__ __forceinline__ int half_blocks(int m, int it, int h) {
-    if constexpr (BF) return m - (2 * it + h) * VShape<R, C>::U;
+    if constexpr (BF || !DShape<R, C>::kAlternate) return m - (2 * it + h) * kUnits<R, C, BF>;
     else return (m - 2 * it * DShape<R, C>::U - h + 1) >> 1;
 }
 
