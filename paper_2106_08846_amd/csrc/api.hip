@@ -257,7 +257,7 @@ bsr_status bsr_spmm_batched_planned(const bsr_spmm_item_t *items, const bsr_plan
     const size_t lds_limit = bsr::device_lds_per_block();
     std::vector<bsr::TiledWork> tiled(work.size());
     std::vector<bsr::KchunkWork> kchunk(work.size());
-    std::vector<bsr::MtileWork> mtile(work.size());
+    std::vector<bsr::MtileWork> mtile;
     std::vector<int> kind(work.size(), kGeneric);
     std::vector<int> tokens(work.size(), 32);   // tokens per tile of a flat or tiled launch
     for (size_t w = 0; w < work.size(); ++w) {
@@ -376,6 +376,7 @@ bsr_status bsr_spmm_batched_planned(const bsr_spmm_item_t *items, const bsr_plan
             const int64_t Nb = it.W->n_rows / it.W->R;
             const int S = slices > 0 ? slices : int(auto_S < Nb ? auto_S : Nb);
             if (kind[w] == kMtile) {
+                mtile.resize(work.size());
                 mtile[w] = bsr::MtileWork{
                     bsr::plan_mtile(it.X, it.T, it.ldx, it.W, it.ldy, S, lds_limit), it.X, it.T,
                     it.ldx, it.W, it.bias, it.Y, it.ldy};
