@@ -180,7 +180,9 @@ struct DShape {
     // 1x4 at 3072 columns, density 0.05, 1881 tokens took 351 us against 236.  Long rows of 1x1
     // blocks gain little, and every other word of a load is loaded for nothing: 264 x 1024, density
     // 0.3, 725 tokens 12.5 us against 10.9 with chunks, 1260 x 3072, 0.05, 1881 tokens 130 and 126.
-    static constexpr bool kAlternate = RC > 1;
+    // With one block per chunk (8x8) the two are the same, but chunks load fewer columns in vain
+    // (768 x 3072, 0.1, 508 tokens 18.2 and 17.9 us).
+    static constexpr bool kAlternate = RC > 1 && U > 1;
     static constexpr int NWV = (NWORDS + 15) / 16;   // weight registers
     static constexpr int VW = VShape<R, C>::VW;
     static_assert(U <= 16 && NWORDS <= 64, "a chunk's columns fit one 16-lane row");
@@ -208,11 +210,13 @@ __device__ __forceinline__ void dload(DOps<R, C> &ops, __amdgpu_buffer_rsrc_t ri
     using S = DShape<R, C>;
     constexpr int RC = S::RC;
     static_assert(RC >= 16 ? RC % 16 == 0 : 16 % RC == 0, "lane i's slot is i / RC past register k's");
-    const int i = threadIdx.x & 15, h = (threadIdx.x & 63) >> 5, base = 2 * it * S::U;
-    ops.j = int(__builtin_amdgcn_raw_buffer_load_b32(
-        ri, (base + (S::kAlternate ? 2 * i + h : S::U * h + i)) * 4, 0, 0));
-    // Alternate blocks: word 16 k + i of slot u = (16 k + i) / RC lies (u + h) RC words further on.
-    const int v0 = (base * RC + (S::kAlternate ? h + i / RC : S::U * h) * RC + i) * 4;
+    const int i = threadIdx.x & 15, h = (threadIdx.x & 63) >> 5;
+    // Column of slot i and word i of the weights; word 16 k + i lies 16 k words further on, and with
+    // alternate blocks another RC words for every slot before its own, (16 k + i) / RC.
+    const int o = S::kAlternate ? 2 * it * S::U + h : (2 * it + h) * S::U;
+    const int j0 = (o + (S::kAlternate ? 2 * i : i)) * 4;
+    const int v0 = (o * RC + (S::kAlternate ? i / RC * RC : 0) + i) * 4;
+    ops.j = int(__builtin_amdgcn_raw_buffer_load_b32(ri, j0, 0, 0));
 #pragma unroll
     for (int k = 0; k < S::NWV; ++k)
         ops.w[k] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(
