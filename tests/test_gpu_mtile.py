@@ -1,10 +1,11 @@
 """The matrix-core kernel for blocks of 4 or 8 rows (4x1, 8x1, 4x4, 8x8) against the oracle.
 
-Sizes sit where it changes course (every product above the work at which the library takes it):
-token tiles of 32 and 64 with tails, one block-row, rows without blocks and full rows next to
+Sizes sit where it changes course (every product above the work at which the library takes it, which
+the tests assert): token tiles of 32 and 64 with tails, one block-row, rows without blocks and full rows next to
 each other (units cut by wave boundaries), many rows per wave, inputs wide enough for several
-column chunks, layers too wide for staged stores, and forced slice counts.  Integer-valued inputs are exact in any order and must equal the generic
-kernel bit for bit; an infinite X element in a column no block reads must not show.
+column chunks, layers too wide for staged stores, forced slice counts, and calls whose products
+share a launch or are split over two.  Integer-valued inputs are exact in any order and must equal
+the generic kernel bit for bit; an infinite X element in a column no block reads must not show.
 """
 import numpy as np
 import pytest
@@ -41,15 +42,23 @@ def inputs(T, K, seed, bf16, integer=False):
 
 CASES = [
     # T, N, K (in blocks of 8), density, skew, slices
-    (22001, 8, 768, 1.0, False, None),  # one 8x8 block-row, the last tile nearly empty
+    (24003, 8, 768, 1.0, False, None),  # one 8x8 block-row, the last tile nearly empty
     (321, 1032, 768, 0.7, False, None), # a last tile of one token
     (200, 2064, 768, 0.5, True, 1),     # one slice: rows cut between waves
     (640, 3072, 136, 0.7, True, 1),     # many rows per wave
-    (97, 1032, 3072, 0.8, True, None),  # several column chunks, few rows per slice
+    (129, 1032, 3072, 0.8, True, None), # several column chunks, few rows per slice
     (450, 768, 1544, 0.5, True, 2),     # chunks, rows cut by waves in every chunk
     (95, 2312, 768, 0.9, False, 72),    # four block-rows of 8 per slice
     (300, 1024, 1024, 0.5, True, 3),    # a tile that leaves no room for staged stores
 ]
+
+
+def assert_enough_work(M, T, bf16):
+    """The product is above the least work of this kernel (below it, another kernel would pass the
+    test): 16 Mi multiply-adds in bf16; 128 Mi in fp32, 192 Mi where the X tile of 32 tokens does not
+    fit in LDS (160 KB) and is cut into column chunks."""
+    least = 16 if bf16 else 192 if 32 * 4 * M.n_cols > 150 * 1024 else 128
+    assert M.nnzb * M.R * M.C * T >= least << 20, "too little work for the kernel under test"
 
 
 @pytest.mark.parametrize("bf16", [False, True], ids=["f32", "bf16"])
@@ -59,6 +68,7 @@ def test_mtile_against_oracle(device, case, R, C, bf16):
     T, N, K, d, skew, slices = CASES[case]
     log(f"mtile {R}x{C} {'bf16' if bf16 else 'f32'} T={T} {N}x{K} d={d} skew={skew} S={slices}")
     M = matrix(N, K, R, C, d, case, skew)
+    assert_enough_work(M, T, bf16)
     bias = np.linspace(-1, 1, N).astype(np.float32)
     X, Xd = inputs(T, K, case, bf16)
     if bf16:
@@ -90,6 +100,7 @@ def test_mtile_infinities_and_pitch(device, R, C, bf16):
     nz = int((np.abs(dense.reshape(N // R, R, K // C, C)).max((1, 3)) > 0).sum())
     M = B.bsr_prune_from_dense(dev(dense), R, C, k=nz)
     assert not (host(M.indices)[:nz] == 0).any()
+    assert_enough_work(M, T, bf16)
     if bf16:
         M = M.to_bf16()
     Xw = X.copy()
@@ -142,3 +153,48 @@ def test_mtile_slices_of_the_launch(device, case):
     check_batch(products[:1], dense, slices=slices)
     check_batch(products, dense, slices=slices)
     check_batch(products[::-1], dense[::-1], slices=slices)
+
+
+# Feed-forward pairs of a 768-wide layer: the second product's input is staged in column chunks.
+#   T, layers as (N, K), density.
+BATCHES = [(777, [(3072, 768), (768, 3072)], 0.2),           # bf16: one launch, staged stores off
+           (4096, [(3072, 768), (768, 3072)], 0.1),          # two launches, one of each kind
+           (4001, [(768, 3072), (768, 768), (1032, 768), (768, 3072)], 0.15),
+           (2051, [(768, 768), (1024, 1024)], 0.3)]          # staged stores fit one product only
+
+
+@pytest.mark.parametrize("bf16", [False, True], ids=["f32", "bf16"])
+@pytest.mark.parametrize("R,C", [(8, 8), (4, 4)], ids=["8x8", "4x4"])
+@pytest.mark.parametrize("case", range(len(BATCHES)))
+def test_mtile_batched(device, case, R, C, bf16):
+    """Several products in one call: whole-row and column-chunked ones in a launch or split over two,
+    against the oracle, and bit for bit against the generic kernel for integer inputs.  A timed call's
+    events span all launches."""
+    T, layers, d = BATCHES[case]
+    log(f"mtile batch {R}x{C} {'bf16' if bf16 else 'f32'} T={T} {layers} d={d}")
+    products, dense, ints = [], [], []
+    for i, (n, k) in enumerate(layers):
+        M = matrix(n, k, R, C, d, 50 + i, i == 0)
+        assert_enough_work(M, T, bf16)
+        X, Xd = inputs(T, k, 50 + i, bf16)
+        bias = dev(np.linspace(-1, 1, n).astype(np.float32))
+        products.append((Xd, M.to_bf16() if bf16 else M, bias, torch.empty((T, n), device="cuda:0")))
+        dense.append(X)
+        M = matrix(n, k, R, C, d, 50 + i, i == 0, integer=True)
+        ints.append((inputs(T, k, 50 + i, bf16, integer=True)[1], M.to_bf16() if bf16 else M, None,
+                     torch.full((T, n), float("nan"), device="cuda:0")))
+    check_batch(products, dense, seed=case)
+    B.bsr_spmm_batched(ints)
+    for Xd, M, _, Y in ints:
+        assert torch.equal(Y, B.bsr_spmm_ex(Xd, M, None, None, kernel=B.KERNEL_GENERIC))
+    call = B.SpmmBatchCall(products)
+    want = [Y.clone() for Y in call()]
+    start, stop = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+    start.record()
+    stop.record()
+    for Y in call.Y:
+        Y.zero_()
+    call.timed(start, stop)
+    stop.synchronize()
+    assert start.elapsed_time(stop) > 0.0
+    assert all(torch.equal(a, b) for a, b in zip(want, call.Y)), "not reproducible"
