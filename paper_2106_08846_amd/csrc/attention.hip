@@ -352,8 +352,13 @@ __global__ __launch_bounds__(64 * kKS) void attention_split_kernel(
 // Every group's output is summed from zero and then added to the running output, so the long sum
 // is rounded once per 32 keys.  Against fp64, 384 tokens x 16 heads, normal inputs: 2-norm error
 // 2.4e-7, where fp32 matrix instructions with one running sum gave 4.5e-7.
-// 16 x 384 tokens, 16 heads: 104 -> 70 us; 8 x 512, 12 heads: 88 -> 61 us (MI355X); what bounds it
+// 16 x 384 tokens, 16 heads: 104 -> 66 us; 8 x 512, 12 heads: 76 -> 56 us (MI355X); what bounds it
 // now is vector instructions (softmax and splitting) and matrix instructions in turn.
+// kAhead: the next block's keys and values are loaded under this block's products, in registers that
+// two waves per SIMD leave free.  With few tiles a workgroup has a SIMD nearly to itself, and waiting
+// for K and then for V in every block made it slower than the fp32 kernel, which loaded both at once
+// (inputs not in the L2: 3 x 262 tokens, 8 heads 25.5 us, fp32 23.3; now 18.9; 1 x 508, 12 heads 38.7,
+// 35.1 and 27.4).
 // Operands have to lie below 2^48, so that no score and no sum over 2^31 keys overflows.  A workgroup
 // that stages any other element (infinities and NaN among them) goes on from that block of keys on
 // fp32 matrix instructions.
@@ -483,7 +488,7 @@ __device__ __forceinline__ float online_softmax(TileState &st, floatx16 &s) {
 // A tile's keys on bf16 pieces.  At the first block with an operand out of the pieces' range (a query
 // counts with the first) it stops and returns false, the block's first key in `left`, in every thread
 // of the workgroup.  The state carries the scales of the weights and the values.
-template <int kWQ, int kKS>
+template <int kWQ, int kKS, bool kAhead>
 __device__ __forceinline__ bool tile_split(TileState &st, const float *qp, const float *Kh,
                                            int64_t ldk, const float *Vh, int64_t ldv, int seq,
                                            float scale, char *smem, int *s_bad, int &left) {
@@ -507,56 +512,89 @@ __device__ __forceinline__ bool tile_split(TileState &st, const float *qp, const
         for (int e = 0; e < 8; ++e) range.add(v[e]);
         split8(v, q[s]);
     }
+    // A block's planes, in chunks of eight elements, one or more of each per thread.  K: row = key, chunk = 8
+    // dimensions.  V: row = output column d, chunk = the 8 keys that one half contracts in one step,
+    // in its registers' order: keys 16 s + 4 h + (0 .. 3) and 16 s + 8 + 4 h + (0 .. 3).  Rows past the
+    // sequence are zero.
+    constexpr int kPer = kAhead ? kKB * 8 / kThreads : 1;
+    static_assert(!kAhead || kPer * kThreads == kKB * 8, "every thread holds kPer chunks of each");
+    float kv[kPer][8], vv[kPer][8];
+    auto each_chunk = [&](auto f) {
+        if constexpr (kAhead) {
+#pragma unroll
+            for (int n = 0; n < kPer; ++n) f(n, tid + n * kThreads);
+        } else {
+            for (int i = tid; i < kKB * 8; i += kThreads) f(0, i);
+        }
+    };
+    auto v_key = [](int c, int e) { return 16 * (c >> 1) + 4 * (c & 1) + (e & 3) + 8 * (e >> 2); };
+    auto load_k = [&](int n, int i, int k0) {
+        const int key = k0 + (i >> 3);
+        const float *kp = Kh + int64_t(key < seq ? key : seq - 1) * ldk + 8 * (i & 7);
+        const floatx4 a = load4(kp), b = load4(kp + 4);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            kv[n][e] = a[e];
+            kv[n][4 + e] = b[e];
+        }
+    };
+    auto load_v = [&](int n, int i, int k0) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const int key = k0 + v_key(i >> 6, e);
+            vv[n][e] = Vh[int64_t(key < seq ? key : seq - 1) * ldv + (i & 63)];
+        }
+    };
+    auto store = [&](const float (&v)[8], char *planes, int r, int c) {
+        uintx4 u[kPieces];
+        split8(v, u);
+#pragma unroll
+        for (int p = 0; p < kPieces; ++p)
+            *reinterpret_cast<uintx4 *>(planes + p * kPlane * 2 + plane_at(r, c)) = u[p];
+    };
+    auto store_k = [&](int n, int i, int k0) {
+        const int r = i >> 3;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) kv[n][e] = k0 + r < seq ? kv[n][e] : 0.0f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) range.add(kv[n][e]);
+        store(kv[n], Kp, r, i & 7);
+    };
+    auto store_v = [&](int n, int i, int k0) {
+        const int c = i >> 6;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) vv[n][e] = k0 + v_key(c, e) < seq ? vv[n][e] : 0.0f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            range.add(vv[n][e]);
+            vv[n][e] *= kValueScale;
+        }
+        store(vv[n], Vp, i & 63, c);
+    };
+    auto load_block = [&](int k0) {
+        each_chunk([&](int n, int i) { load_k(n, i, k0); });
+        each_chunk([&](int n, int i) { load_v(n, i, k0); });
+    };
     if (tid == 0) *s_bad = 0;
+    if constexpr (kAhead) load_block(0);
     for (int k0 = 0; k0 < seq; k0 += kKB) {
         __syncthreads();   // the previous block's LDS reads are done
-        // K: row = key, chunk = 8 dimensions.  V: row = output column d, chunk = the 8 keys that
-        // one half contracts in one step, in its registers' order: keys 16 s + 4 h + (0 .. 3) and
-        // 16 s + 8 + 4 h + (0 .. 3).  Rows past the sequence are zero.
-        for (int i = tid; i < kKB * 8; i += kThreads) {
-            const int r = i >> 3, c = i & 7, key = k0 + r;
-            float v[8];
-            const float *kp = Kh + int64_t(key < seq ? key : seq - 1) * ldk + 8 * c;
-            const floatx4 a = load4(kp), b = load4(kp + 4);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                v[e] = key < seq ? a[e] : 0.0f;
-                v[4 + e] = key < seq ? b[e] : 0.0f;
-            }
-#pragma unroll
-            for (int e = 0; e < 8; ++e) range.add(v[e]);
-            uintx4 u[kPieces];
-            split8(v, u);
-#pragma unroll
-            for (int p = 0; p < kPieces; ++p)
-                *reinterpret_cast<uintx4 *>(Kp + p * kPlane * 2 + plane_at(r, c)) = u[p];
-        }
-        for (int i = tid; i < kD * 8; i += kThreads) {
-            const int d = i & 63, c = i >> 6, base = k0 + 16 * (c >> 1) + 4 * (c & 1);
-            float v[8];
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const int key = base + (e & 3) + 8 * (e >> 2);
-                const float x = Vh[int64_t(key < seq ? key : seq - 1) * ldv + d];
-                v[e] = key < seq ? x : 0.0f;
-            }
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                range.add(v[e]);
-                v[e] *= kValueScale;
-            }
-            uintx4 u[kPieces];
-            split8(v, u);
-#pragma unroll
-            for (int p = 0; p < kPieces; ++p)
-                *reinterpret_cast<uintx4 *>(Vp + p * kPlane * 2 + plane_at(d, c)) = u[p];
-        }
+        each_chunk([&](int n, int i) {
+            if constexpr (!kAhead) load_k(n, i, k0);
+            store_k(n, i, k0);
+        });
+        each_chunk([&](int n, int i) {
+            if constexpr (!kAhead) load_v(n, i, k0);
+            store_v(n, i, k0);
+        });
         if (range.outside()) *s_bad = 1;
         __syncthreads();
         if (*s_bad) {   // the same word in every thread
             left = k0;
             return false;
         }
+        // The next block's loads, under this block's products.
+        if (kAhead && k0 + kKB < seq) load_block(k0 + kKB);
 
 #pragma unroll
         for (int gi = 0; gi < kKB / 32 / kKS; ++gi) {
@@ -681,8 +719,8 @@ __device__ __forceinline__ void tile_fp32(TileState &st, const float *qp, const 
 constexpr int kMfmaLds = 2 * kPieces * kPlane * 2;
 static_assert(2 * kKB * kPitch * 4 <= kMfmaLds, "the fp32 tiles fit");
 
-template <int kWQ, int kKS>
-__global__ __launch_bounds__(kWQ * kKS * 64) __attribute__((amdgpu_waves_per_eu(3)))
+template <int kWQ, int kKS, bool kAhead = false>
+__global__ __launch_bounds__(kWQ * kKS * 64) __attribute__((amdgpu_waves_per_eu(kAhead ? 2 : 3)))
 void attention_mfma_kernel(
     const float *__restrict__ Q, int64_t ldq, const float *__restrict__ K, int64_t ldk,
     const float *__restrict__ V, int64_t ldv, float *__restrict__ O, int64_t ldo, int seq,
@@ -702,7 +740,7 @@ void attention_mfma_kernel(
     TileState st;
     tile_reset(st);
     int left = 0;
-    if (!tile_split<kWQ, kKS>(st, qp, Kh, ldk, Vh, ldv, seq, scale, smem, &s_bad, left)) {
+    if (!tile_split<kWQ, kKS, kAhead>(st, qp, Kh, ldk, Vh, ldv, seq, scale, smem, &s_bad, left)) {
         st.l *= 1.0f / kWeightScale;
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
@@ -783,8 +821,10 @@ bsr_status launch_attention(const float *Q, int64_t ldq, const float *K, int64_t
             return launch_status();
         };
         // Under three tiles per CU (or tiles too few to share staged keys) two waves split each
-        // tile's keys: 1 x 512 tokens 32 us against 43 with one wave per tile.
-        if (tiles32 < 3 * cus || nt < 4) return go(attention_mfma_kernel<2, 2>, 2, 2);
+        // tile's keys: 1 x 512 tokens 32 us against 43 with one wave per tile.  Loading ahead takes
+        // registers for at most 1.5 workgroups per CU, all that there are below three tiles.
+        if (tiles32 < 3 * cus) return go(attention_mfma_kernel<2, 2, true>, 2, 2);
+        if (nt < 4) return go(attention_mfma_kernel<2, 2>, 2, 2);
         // Else 12, 8 or 4 tiles share a workgroup's staged keys, whichever leaves the fewest waves
         // on the busiest SIMD; staging costs about a tenth and three tenths more for 8 and 4 tiles
         // (12 / 8 / 4 tiles: 16 x 384 tokens, 16 heads 70 / 92 / 80 us; 8 x 512, 12 heads
