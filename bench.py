@@ -638,8 +638,8 @@ def kernel_name(c, bf16: bool, planned: bool = False, persistent: bool = False,
     for 32x1 and 16x1 (its planned form with a plan), the matrix-core tiled kernel for square
     blocks, the small-block matrix-core kernel for blocks of 4 or 8 rows and enough work, else
     the vector-ALU tile kernel, each in its column-chunked form when the X tile does not fit in
-    LDS, else the generic kernel.  (A label: the library's plan decides,
-    and the kernel trace shows what ran.)"""
+    LDS, else the generic kernel.  (A label: the library's plan decides, and the kernel trace
+    shows what ran.)"""
     shape = (c["R"], c["C"])
     flag = "true" if bf16 else "false"
     xb = 2 if bf16 and shape != (16, 1) else 4
@@ -659,10 +659,14 @@ def kernel_name(c, bf16: bool, planned: bool = False, persistent: bool = False,
         if fits:
             return f"spmm_tiled_kernel<{c['R']}, {c['C']}, 16, {flag}, {w}>"
         return f"spmm_kchunk_kernel<{c['R']}, {c['C']}, {flag}, {w}>"
-    macs = c["k"] * c["R"] * c["C"] * c["T"]
     if shape in ((8, 8), (4, 4), (8, 1), (4, 1)):
-        if macs >= ((16 if bf16 else 128 if fits else 192) << 20):
-            return f"spmm_mtile_kernel<{c['R']}, {c['C']}, {flag}, {'false' if fits else 'true'}>"
+        # Its X tile takes 128 bytes per column: 64 tokens of bf16 (blocks of 4 or 8 columns) or 32 of
+        # fp32.  Whether whole-row products run in their column-chunked form and with staged stores
+        # depends on the launch; the label leaves those two arguments out.
+        whole = 128 * (c["K"] + c["C"]) + 4 * c["N"] + 8 * (c["N"] // c["R"]) <= 160 * 1024
+        macs = c["k"] * c["R"] * c["C"] * c["T"]
+        if macs >= ((16 if bf16 else 128 if whole else 192) << 20):
+            return f"spmm_mtile_kernel<{c['R']}, {c['C']}, {flag}, ...>"
     if shape in VALU_SHAPES and not (bf16 and shape == (1, 1)):
         kern = "spmm_vtile_kernel" if fits else "spmm_vtile_chunk_kernel"
         return f"{kern}<{c['R']}, {c['C']}, {flag}>"

@@ -44,8 +44,11 @@ __device__ __forceinline__ int clampi(int v, int lo, int hi) {
 __device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
 
 // Raw buffer resource over [base, base + bytes): loads past the end return 0 and stores past
-// it are dropped.  Word 3 is the default raw-buffer configuration for gfx9-family chips.  The
-// launch plans keep every range below 2^31 bytes.
+// it are dropped.  The check covers the vector, instruction and scalar offsets together, word by
+// word, also where the scalar offset alone is past the end (MI355X, a range inside a larger
+// allocation, 16-byte loads and 4-byte stores at scalar offsets from 0 to 64 times the range).  Word
+// 3 is the default raw-buffer configuration for gfx9-family chips.  The launch plans keep every range
+// below 2^31 bytes.
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_rsrc(const void *base, unsigned bytes) {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, int(bytes), 0x00020000);
 }

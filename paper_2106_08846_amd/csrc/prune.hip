@@ -1179,9 +1179,11 @@ constexpr int kRowThreads = 256;
 constexpr int kRowWaves = kRowThreads / 64;
 
 // Per-row selection: workgroup i keeps the k_row blocks of block-row i that come first in the
-// order (key descending, column ascending), with the radix select and id-order sweep of
-// prune_select_kernel restricted to the row.  Every row keeps k_row blocks, so indptr[i] is
-// i * k_row and the kept blocks of row i occupy positions i * k_row .. (i + 1) * k_row - 1.
+// order (key descending, column ascending).  A radix select over the row's keys, eight bits a pass
+// from the top, gives the k_row-th largest key and how many of its equals are kept; a sweep over the
+// columns then counts equals and kept blocks and writes the kept ones in place.  Every row keeps k_row
+// blocks, so indptr[i] is i * k_row and the kept blocks of row i occupy positions i * k_row ..
+// (i + 1) * k_row - 1.
 __global__ __launch_bounds__(kRowThreads) void prune_select_rows_kernel(
     const unsigned long long *__restrict__ keybits, int64_t Kb, int64_t Nb, int64_t k_row,
     int32_t *__restrict__ indptr, int32_t *__restrict__ indices, int32_t *__restrict__ src) {
@@ -1324,7 +1326,7 @@ bsr_status launch_prune(const float *W, int64_t N, int64_t K, int64_t ldw, int32
     auto *src = reinterpret_cast<int32_t *>(base + ws.src_offset);
     hipStream_t st = as_stream(stream);
 
-    // Global selection over more keys than one workgroup's registers hold: spread over the chip.
+    // Global selection over more keys than one workgroup's LDS holds codes of: spread over the chip.
     if (select == BSR_SELECT_GLOBAL && k > 0 && nb > int64_t(kSelThreads) * kRegKeys)
         return launch_prune_wide(W, ldw, R, C, Kb, Nb, nb, k, keybits, src, indptr, indices, data,
                                  norm, st);
@@ -1352,7 +1354,8 @@ bsr_status launch_prune(const float *W, int64_t N, int64_t K, int64_t ldw, int32
                            src);
     else
         hipLaunchKernelGGL(prune_select_kernel, dim3(1), dim3(kSelThreads),
-                           k > 0 ? select_lds_bytes(nb) : 0, st, keybits, nb, Kb, Nb, k, indptr, indices, src);
+                           k > 0 ? select_lds_bytes(nb) : 0, st, keybits, nb, Kb, Nb, k, indptr,
+                           indices, src);
     bsr_status s = launch_status();
     if (s != BSR_OK || k == 0) return s;
     hipLaunchKernelGGL(prune_copy_kernel, dim3(grid_for(k * R * C, 256)), dim3(256), 0, st, W,

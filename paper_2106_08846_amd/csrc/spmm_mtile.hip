@@ -436,8 +436,9 @@ __global__ __launch_bounds__(kNW * 64) void spmm_mtile_kernel(const MtileBatch b
                     const __amdgpu_buffer_rsrc_t ri = buffer_rsrc(indices, unsigned(lend) * 4u);
                     const __amdgpu_buffer_rsrc_t rd =
                         buffer_rsrc(data, unsigned(lend) * unsigned(RC * S::kEs));
-                    // lp goes into the vector offsets: the range check need not cover a scalar one
-                    // (2-4% faster for 8x1 blocks; a range that starts at lp was slower still).
+                    // lp goes into the vector offsets; in the scalar offset, which is range-checked as
+                    // well, it measured within 2% either way (3072 x 768, 4096 tokens, 8x1 fp32 42.0
+                    // / 41.4 us, bf16 39.0 / 39.3).  A range that starts at lp was slower.
                     o.j = __builtin_amdgcn_raw_buffer_load_b32(ri, vj + lp * 4, 0, 0);
                     const int so = lp * (RC * S::kEs);
 #pragma unroll
@@ -614,8 +615,9 @@ __global__ __launch_bounds__(kNW * 64) void spmm_mtile_kernel(const MtileBatch b
 }
 
 // Least multiply-adds (stored weights x tokens) of a product for this kernel, by the plan that it
-// would have in a launch of its own; smaller ones keep the vector-ALU kernels, whose prologue is shorter (no unit tables, shares or combine).  Measured on
-// MI355X at a density of 0.1, vector-ALU / this kernel in us, 8x8 and 4x4 blocks:
+// would have in a launch of its own; smaller ones keep the vector-ALU kernels, whose prologue is
+// shorter (no unit tables, shares or combine).  Measured on MI355X at a density of 0.1, vector-ALU /
+// this kernel in us, 8x8 and 4x4 blocks:
 //   fp32  768x768, 777 tokens (46 M): 7.8 / 8.3, 7.4 / 8.4;  3072x768, 777 tokens (183 M):
 //         15.8 / 13.8, 17.2 / 15.8;  768x3072 (chunked, 183 M): 21.0 / 20.6, 19.8 / 20.9;
 //         3072x768, 4096 tokens: 52.8 / 36.8, 66.3 / 46.1;  768x3072: 76.6 / 45.6, 84.2 / 55.6.

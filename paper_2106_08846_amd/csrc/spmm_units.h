@@ -481,7 +481,7 @@ struct Unit64BF {
 // weights) and no operand is masked or re-arranged at run time.  The sums are those of the
 // unplanned unit of the same shape: the same blocks in the same k-slots of the same
 // instructions.  Loads of a unit at or past `ulim` fetch nothing and return 0 (the unit's
-// offset is in the range-checked vector offset).
+// offset is range-checked).
 template <int R, int C, bool BF>
 struct PlanUnit;
 
