@@ -352,7 +352,7 @@ __global__ __launch_bounds__(64 * kKS) void attention_split_kernel(
 // Every group's output is summed from zero and then added to the running output, so the long sum
 // is rounded once per 32 keys.  Against fp64, 384 tokens x 16 heads, normal inputs: 2-norm error
 // 2.4e-7, where fp32 matrix instructions with one running sum gave 4.5e-7.
-// 16 x 384 tokens, 16 heads: 104 -> 66 us; 8 x 512, 12 heads: 76 -> 56 us (MI355X); what bounds it
+// 16 x 384 tokens, 16 heads: 104 -> 66 us; 8 x 512, 12 heads: 76 -> 53 us (MI355X); what bounds it
 // now is vector instructions (softmax and splitting) and matrix instructions in turn.
 // kAhead: the next block's keys and values are loaded under this block's products, in registers that
 // two waves per SIMD leave free.  With few tiles a workgroup has a SIMD nearly to itself, and waiting
@@ -429,12 +429,12 @@ __device__ __forceinline__ floatx16 mfma_split(const uintx4 (&a)[kPieces],
 
 // 2^24 exp(x) for x <= 0: 2^u of u = x log2(e) + 24, rounded to z + 24 with z = u - 24 exact, times
 // 1 + r ln 2 for what the roundings and log2(e)'s low bits left out (r < 2^-16 where exp(x) is not
-// negligible).  About half of expf's instructions: x is never positive, so nothing overflows; and the
-// 2^24 inside the hardware's 2^u, which is never a subnormal number, keep the smallest weights.
+// negligible).  About half of expf's instructions: x is never positive and above -2^121, so nothing
+// overflows (where 2^u is 0, r is finite).  The 2^24 inside the hardware's 2^u, which is never a
+// subnormal number, keep the smallest weights.
 __device__ __forceinline__ float exp_scaled(float x) {
 #pragma clang fp contract(off)
     constexpr float kLog2e = 0x1.715476p+0f, kLog2eLo = 0x1.4ae0bfp-26f, kLn2 = 0x1.62e430p-1f;
-    x = fmaxf(x, -200.0f);   // -inf has no remainder; the weight is 0 either way
     const float t = x * kLog2e, u = t + kWeightExp, z = u - kWeightExp;
     float r = __builtin_fmaf(x, kLog2e, -z);
     r = __builtin_fmaf(x, kLog2eLo, r);
@@ -454,12 +454,14 @@ __device__ __forceinline__ void tile_reset(TileState &st) {
     for (int v = 0; v < 16; ++v) st.o0[v] = st.o1[v] = 0.0f;
 }
 
-// Keys past the sequence get a score of -inf (weight 0); a group's first key exists.
+// Keys past the sequence get a score of weight 0: -inf, or -2^120 for exp_scaled, which is below every
+// score of operands under 2^48.  A group's first key exists.
+template <bool kSplit>
 __device__ __forceinline__ void mask_keys(floatx16 &s, int kg, int hh, int seq) {
     if (kg + 32 > seq) {
 #pragma unroll
         for (int v = 0; v < 16; ++v)
-            if (kg + 8 * (v >> 2) + 4 * hh + (v & 3) >= seq) s[v] = -INFINITY;
+            if (kg + 8 * (v >> 2) + 4 * hh + (v & 3) >= seq) s[v] = kSplit ? -0x1p120f : -INFINITY;
     }
 }
 
@@ -515,12 +517,14 @@ __device__ __forceinline__ bool tile_split(TileState &st, const float *qp, const
     // A block's planes, in chunks of eight elements, one or more of each per thread.  K: row = key, chunk = 8
     // dimensions.  V: row = output column d, chunk = the 8 keys that one half contracts in one step,
     // in its registers' order: keys 16 s + 4 h + (0 .. 3) and 16 s + 8 + 4 h + (0 .. 3).  Rows past the
-    // sequence are zero.
-    constexpr int kPer = kAhead ? kKB * 8 / kThreads : 1;
-    static_assert(!kAhead || kPer * kThreads == kKB * 8, "every thread holds kPer chunks of each");
+    // sequence are zero.  With one chunk of each per thread (eight tiles) K and V are loaded together
+    // (8 x 512 tokens, 12 heads 55.3 -> 53.4 us); elsewhere that spilled.
+    constexpr bool kBoth = kAhead || kThreads == kKB * 8;   // K and V in registers at once
+    constexpr int kPer = kBoth ? kKB * 8 / kThreads : 1;
+    static_assert(!kBoth || kPer * kThreads == kKB * 8, "every thread holds kPer chunks of each");
     float kv[kPer][8], vv[kPer][8];
     auto each_chunk = [&](auto f) {
-        if constexpr (kAhead) {
+        if constexpr (kBoth) {
 #pragma unroll
             for (int n = 0; n < kPer; ++n) f(n, tid + n * kThreads);
         } else {
@@ -579,12 +583,13 @@ __device__ __forceinline__ bool tile_split(TileState &st, const float *qp, const
     if constexpr (kAhead) load_block(0);
     for (int k0 = 0; k0 < seq; k0 += kKB) {
         __syncthreads();   // the previous block's LDS reads are done
+        if constexpr (kBoth && !kAhead) load_block(k0);
         each_chunk([&](int n, int i) {
-            if constexpr (!kAhead) load_k(n, i, k0);
+            if constexpr (!kBoth) load_k(n, i, k0);
             store_k(n, i, k0);
         });
         each_chunk([&](int n, int i) {
-            if constexpr (!kAhead) load_v(n, i, k0);
+            if constexpr (!kBoth) load_v(n, i, k0);
             store_v(n, i, k0);
         });
         if (range.outside()) *s_bad = 1;
@@ -613,7 +618,7 @@ __device__ __forceinline__ bool tile_split(TileState &st, const float *qp, const
                         Kp + p * kPlane * 2 + plane_at(32 * g + ql, 2 * st4 + hh));
                 s = mfma_split(a, q[st4], s);
             }
-            mask_keys(s, kg, hh, seq);
+            mask_keys<true>(s, kg, hh, seq);
             const float corr = online_softmax<true>(st, s);
             uintx4 w2[2][kPieces];
 #pragma unroll
@@ -698,7 +703,7 @@ __device__ __forceinline__ void tile_fp32(TileState &st, const float *qp, const 
                 for (int e = 0; e < 4; ++e)
                     s = __builtin_amdgcn_mfma_f32_32x32x2f32(kv[e], q[d + e], s, 0, 0, 0);
             }
-            mask_keys(s, kg, hh, seq);
+            mask_keys<false>(s, kg, hh, seq);
             const float corr = online_softmax<false>(st, s);
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
