@@ -19,7 +19,8 @@ the durations that HIP events recorded at each product kernel's own start and en
 (hipExtLaunchKernel) are reported beside it.
 
 Beside the headline, unless --no-rows, the same line carries the block-shape rows of the other
-configurations, each timed per launch with those kernel events and reported as median, p10, p90:
+configurations, each timed per launch with those kernel events (medians, roof fractions and the
+ratio to the dense GEMM; --rows-file writes every row in full, percentiles included):
   * the BERT-large 32x32 stack (fp32 matrix cores), cold by construction like the headline;
   * the fused QKV weight 2304x768 at 4096 tokens, 32x1 and 16x16 blocks at 5-40% density, fp32
     and bf16, cold: 8 rotating copies of (X, BSR, bias, Y), 400 MB or more in all;
@@ -80,6 +81,9 @@ def parse(argv=None):
                     help="time the step as HIP graph replays instead of direct calls")
     ap.add_argument("--no-rows", action="store_true",
                     help="headline only: skip the block-shape rows of the other workloads")
+    ap.add_argument("--rows-file", metavar="PATH",
+                    help="write the block-shape rows in full (percentiles, rates, protocol) as "
+                         "JSON to PATH; the result line carries their main figures")
     ap.add_argument("--cpu-seconds", type=float, default=10.0,
                     help="approximate CPU time spent timing the oracle on the headline sample")
     ap.add_argument("--no-cpu-baseline", action="store_true")
@@ -496,6 +500,30 @@ def rows(args) -> dict:
     return res
 
 
+def short_rows(res: dict) -> dict:
+    """The rows' main figures for the result line: whoever runs the benchmark may keep only the end
+    of its output, and the rows in full are 28 KB.  Four significant digits; per product row the
+    kernel-event median and the back-to-back time per launch in us, the binding roof and the
+    fraction of it, and the ratio to the dense GEMM of the same shape."""
+    def sig(x):
+        return float(f"{x:.4g}")
+
+    def short(r):
+        if "launch_us" not in r:
+            return {"workload": r["workload"], "us_per_iteration": sig(r["us_per_iteration"]),
+                    "loss_one_shot": r["loss_one_shot"], "loss_after": r["loss_after"],
+                    "cpu_oracle_ms_per_iteration": sig(r["cpu_oracle_ms_per_iteration"])}
+        split = r["plan_arithmetic"] not in (None, "native")
+        s = {"row": r["spec"] + (" split" if split else ""), "us": sig(r["launch_us"]["median"]),
+             "loop_us": sig(r["loop_us_per_launch"]), "bound": r["roof"]["bound"],
+             "frac": sig(r["roof"]["frac"])}
+        if "sparse_over_dense" in r:
+            s["vs_dense"] = sig(r["sparse_over_dense"])
+        return s
+
+    return {k: [short(r) for r in v] for k, v in res.items()}
+
+
 def iht_row(R: int, C: int, density: float, iters: int = 20) -> dict:
     """The iterative projection for Eq. 2 on one BERT-base projection (768 x 768, the Q weight
     of the BERT-base workload) with the reconstruction loss of 4096 synthetic calibration
@@ -785,7 +813,11 @@ def main(argv=None) -> int:
 
     if not args.no_rows:
         print("# rows", file=sys.stderr, flush=True)
-        out["rows"] = rows(args)
+        full = rows(args)
+        out["rows"] = short_rows(full)
+        if args.rows_file:
+            with open(args.rows_file, "w") as f:
+                json.dump(full, f, indent=1)
     if not args.no_cpu_baseline:
         print("# cpu baseline", file=sys.stderr, flush=True)
         out["cpu_baseline"] = cpu_baseline(wl, args.cpu_seconds)
